@@ -55,7 +55,7 @@ FORCE_TRAFFIC = {  # (precision, evaluator) -> counters of the step's force kern
 # Lane-operation issue peak of the vector ALUs: 256 CUs x 4 SIMDs x 16 lanes x
 # 2.4 GHz (FP64 and unpacked FP32 issue at the same rate; packed FP32 is off).
 VALU_PEAK_LANE_OPS = 256 * 4 * 16 * 2.4e9
-FORCE_SOURCES = ["paper_1107_2619_amd/csrc/kernels.hip", "paper_1107_2619_amd/csrc/kernels_brick.hip",
+FORCE_SOURCES = ["paper_1107_2619_amd/csrc/kernels_global.h", "paper_1107_2619_amd/csrc/kernels_brick.hip",
                  "paper_1107_2619_amd/csrc/md_device.h", "paper_1107_2619_amd/csrc/md_internal.h"]
 # The paper's own timings (section "Parallel benchmarks"), quoted as context
 # only: they are FP64 runs of a Fortran 95 / OpenMP code on other hardware and

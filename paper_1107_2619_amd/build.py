@@ -15,8 +15,9 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmdeam.so")
-SOURCES = ["kernels.hip", "kernels_build.hip", "kernels_brick.hip", "kernels_pairs.hip", "kernels_analysis.hip", "kernels_box.hip",
-           "md_runtime.hip"]
+SOURCES = ["kernels.hip", "kernels_global_f64.hip", "kernels_global_f64_multi.hip", "kernels_global_mixed.hip",
+           "kernels_global_mixed_multi.hip", "kernels_build.hip", "kernels_brick.hip", "kernels_pairs.hip", "kernels_analysis.hip",
+           "kernels_box.hip", "md_runtime.hip"]
 ARCH = "gfx950"
 
 

@@ -1,18 +1,7 @@
-// gfx950 kernels of the embedded-atom force loop.
-//
-// Global-gather kernels (the list build is in kernels_build.hip).  Data
-// layout (all in the caller-provided workspace, see md_runtime.hip):
-//   - atoms live in "slots" sorted by link cell (paper, "OpenMP
-//     Parallelisation": particles ordered by link-cell index so cell members
-//     are contiguous); replica r owns a wavefront-aligned slot range;
-//   - positions as double4 {x, y, z, F'}: one 32-byte gather per neighbour
-//     brings the position and the embedding derivative the force pass needs;
-//   - the Verlet list is one int32 row per atom (slot index + periodic shift
-//     code), read 8 entries per two 16-byte loads;
-//   - the full (symmetric) list lets each atom gather its own density and
-//     force with no atomics; the half list with FP64 atomics is kept as the
-//     comparison variant (paper, "OpenMP Parallelisation", on the trade
-//     between a symmetric list and synchronised updates).
+// gfx950 kernels of the embedded-atom force loop: slot and state setup, the
+// energy reductions, the thermostat, the barostat on orthorhombic boxes and the
+// Gear integrator (the density and force passes are in kernels_global.h, the
+// list build in kernels_build.hip).
 #include "md_device.h"
 
 namespace mdk {
@@ -94,290 +83,6 @@ __global__ void k_compact_records(Buffers b, int p, int64_t n_slots)
     int4 rq;
     if (!compact_coords(R, c, x.x, x.y, x.z, rq)) atomicAdd(&b.flags[F_COMPACT], 1);
     b.rec[0][t] = rq;
-}
-
-// Pair separation from compact records.  With the cell offset dc in {-1,0,1}
-// per axis, d_a = (q_j - q_i + dc 2^28) h_a 2^-28: the integer part is exact
-// in 32 bits (|d| < 8 cells), and the scale is one rounding in FP64.  `qi1`
-// holds q_i + 2^28, so the field c = dc + 1 of the entry adds c 2^28.
-__device__ __forceinline__ double compact_axis(int code_field, int qj, int qi1, double qs)
-{
-    const uint32_t dq = ((uint32_t)code_field << kCompactBits) + (uint32_t)qj - (uint32_t)qi1;
-    return (double)(int32_t)dq * qs;
-}
-
-// CMP = 1: orthorhombic cells.  CMP = 2: a sheared cell, whose records hold
-// fractional in-cell coordinates: the integer differences along the three edge
-// vectors map through qg = h diag(2^-28 / n_a) into the Cartesian separation.
-template <int CMP>
-__device__ __forceinline__ void compact_delta(const DevReplica& R, const int4& qi1, const int4& qj, int code,
-                                              double& dx, double& dy, double& dz)
-{
-    if (CMP == 2) {
-        const double d0 = compact_axis(code & 3, qj.x, qi1.x, 1.0);
-        const double d1 = compact_axis((code >> 2) & 3, qj.y, qi1.y, 1.0);
-        const double d2 = compact_axis((code >> 4) & 3, qj.z, qi1.z, 1.0);
-        dx = fma(R.qg[0], d0, fma(R.qg[1], d1, R.qg[2] * d2));
-        dy = fma(R.qg[3], d0, fma(R.qg[4], d1, R.qg[5] * d2));
-        dz = fma(R.qg[6], d0, fma(R.qg[7], d1, R.qg[8] * d2));
-        return;
-    }
-    dx = compact_axis(code & 3, qj.x, qi1.x, R.qs[0]);
-    dy = compact_axis((code >> 2) & 3, qj.y, qi1.y, R.qs[1]);
-    dz = compact_axis((code >> 4) & 3, qj.z, qi1.z, R.qs[2]);
-}
-
-__device__ __forceinline__ int4 compact_base(const int4& q)
-{
-    constexpr int one = 1 << kCompactBits;
-    return make_int4(q.x + one, q.y + one, q.z + one, q.w);
-}
-
-// One 16-byte gather through a raw buffer resource: a single load
-// instruction with a 32-bit offset (out-of-range offsets read zero).
-typedef int int4v __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t record_rsrc(const int4* p, int64_t n)
-{
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<int4*>(p), (short)0, (int)(n * 16), (int)kBufferWord3);
-}
-__device__ __forceinline__ int4 record_load(__amdgpu_buffer_rsrc_t rs, int j)
-{
-    const int4v v = __builtin_amdgcn_raw_buffer_load_b128(rs, j * 16, 0, 0);
-    return make_int4(v.x, v.y, v.z, v.w);
-}
-
-// ---------------------------------------------------------------------------
-// Global-gather kernels: one thread per atom reads its neighbours straight
-// from the cache hierarchy through the transposed int32 list.  Neighbours go
-// in chunks of kChunk: all index loads, then all gathers, then the
-// arithmetic.  Entries past the end point at the atom itself (masked).
-//
-// The cost of these loops is set by the number of vector-memory accesses per
-// neighbour (the L1 resolves about one cache-line access per clock per CU),
-// not by bytes or arithmetic: FP64 mode gathers a 32-byte {x, y, z, F'} record
-// (two accesses), the compact mixed mode a 16-byte record (one access).
-//
-// Density pass (Eq. Ucoh, the argument of F): rho_i = sum_j rho_{s_i s_j}(r_ij),
-// then F_i and F'_i.  The sum is accumulated in FP64 in both precision modes.
-//
-// NCH: neighbour records in flight per thread (2, 4 or 8; the autotuner picks
-// it): more hide more gather latency, fewer free registers for more waves.
-//
-// TL: several species with all their tables staged in LDS, in workgroups of
-// kTableBlock threads that share one copy (one species always stages its own).
-template <typename R, bool SINGLE, int NPK, int NDK, int EV, int CMP, int NCH, bool TL>
-__global__ __launch_bounds__(TL ? kTableBlock : kBlock) void k_density(Buffers b, int p, int q, int64_t n_slots,
-                                                                        PotArgs P, int energy)
-{
-    extern __shared__ __align__(16) unsigned char smem[];
-    const R* tab = tables<R>(b).dens;
-    if (EV != EV_KNOTS && (SINGLE || TL)) {
-        R* s = reinterpret_cast<R*>(smem);
-        lds_fill(s, tab, (SINGLE ? 1 : P.ns * P.ns) * P.nbt * value_stride(EV));
-        __syncthreads();
-        tab = s;
-    }
-    const int64_t t = global_thread();
-    if (t >= n_slots) return;
-    const DevReplica& Rp = b.reps[uniform(b.rep_of_wave[t / kWave])];
-    if (t - Rp.slot_off >= Rp.n_atoms) return;
-    const Box bx = load_box(Rp);
-    const DevPotential& G = *b.pot;
-    const double4* __restrict__ pos = b.pos[p];
-    const int4* __restrict__ rec = b.rec[0];
-    const int32_t* __restrict__ nbr = b.nbr;
-    const double3 xi = CMP ? make_double3(0.0, 0.0, 0.0) : load_xyz(pos, t);
-    const int4 qi = CMP ? rec[t] : make_int4(0, 0, 0, 0);
-    const int4 qb = compact_base(qi);
-    const __amdgpu_buffer_rsrc_t rs = record_rsrc(b.rec[0], n_slots);
-    const int si = b.type[q][t] & 0x3F;
-    const int n = b.ncount[t];
-    double rho = 0.0;
-    constexpr int GR = NCH >= kChunk ? NCH / kChunk : 1;  // list groups per iteration
-    constexpr int SUB = NCH >= kChunk ? 1 : kChunk / NCH;  // record batches per group
-    static_assert(kChunk == 4 && NCH * SUB == kChunk * GR, "one int4 list load per four entries");
-    for (int k0 = 0; k0 < n; k0 += kChunk * GR) {
-        int v[kChunk * GR];
-#pragma unroll
-        for (int g = 0; g < GR; ++g) {  // 16-byte loads of four entries; groups past cap are padding
-            const int4 v4 = reinterpret_cast<const int4*>(nbr)[(int64_t)((k0 >> 2) + g) * n_slots + t];
-            v[4 * g] = v4.x;
-            v[4 * g + 1] = v4.y;
-            v[4 * g + 2] = v4.z;
-            v[4 * g + 3] = v4.w;
-        }
-        uint32_t tv[GR];  // neighbour type bytes of the groups (several species)
-#pragma unroll
-        for (int g = 0; g < GR; ++g)
-            tv[g] = SINGLE ? 0u : reinterpret_cast<const uint32_t*>(b.ntype)[(int64_t)((k0 >> 2) + g) * n_slots + t];
-#pragma unroll
-        for (int sb = 0; sb < SUB; ++sb) {
-            const int kb = k0 + sb * NCH;
-            if (kb >= n) break;
-            int e[NCH];
-            double3 xs[NCH];
-            int4 qs[NCH];
-#pragma unroll
-            for (int u = 0; u < NCH; ++u) {
-                // FP64: only inner entries (the others lie beyond every density
-                // cutoff); mixed-precision lists mark every entry inner
-                e[u] = kb + u < n ? v[sb * NCH + u] : (int)t;
-                if (sizeof(R) == 4 || e[u] < 0) {
-                    if (CMP) qs[u] = record_load(rs, e[u] & kIndexMask);
-                    else xs[u] = load_xyz(pos, e[u] & kIndexMask);
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < NCH; ++u) {
-                if (kb + u >= n) break;
-                if (sizeof(R) == 8 && e[u] >= 0) continue;
-                const int code = ((unsigned)e[u] >> kIndexBits) & kCodeMask;
-                double dx, dy, dz;
-                if (CMP) {
-                    compact_delta<CMP>(Rp, qb, qs[u], code, dx, dy, dz);
-                } else {
-                    dx = xs[u].x - xi.x;
-                    dy = xs[u].y - xi.y;
-                    dz = xs[u].z - xi.z;
-                    if (code) apply_shift(bx, code, dx, dy, dz);
-                }
-                const double r2 = fma(dx, dx, fma(dy, dy, dz * dz));
-                if (!(r2 < P.rc2)) continue;
-                const double r = r2 * inv_dist<R>(r2);
-                const int ku = sb * NCH + u;  // entry within the groups loaded
-                const int sj = SINGLE ? 0 : (int)((tv[ku >> 2] >> (8 * (ku & 3))) & 0x3F);
-                rho += (double)density_term<R, SINGLE, NDK, EV>(P, G, tab, si, sj, r);
-            }
-        }
-    }
-    double F, dF;
-    embed(SINGLE ? P.emb_c : G.emb_c[si], rho, F, dF);
-    if (CMP) b.rec[1][t] = make_int4(qi.x, qi.y, qi.z, __float_as_int((float)dF));
-    else reinterpret_cast<double*>(b.pos[p] + t)[3] = dF;
-    if (energy) b.femb[t] = F;
-}
-
-// Force pass + velocity Verlet (global gathers).
-//
-// EN = 4: the energies and virial of energy mode 1, summed per wavefront in the
-// kernel (the reduction then reads one record per 64 atoms).
-template <typename R, bool SINGLE, int NPK, int NDK, int EV, int EN, bool CLOSE, bool OPEN, bool WRITEBACK,
-          int CMP, int NCH, bool TL>
-__global__ __launch_bounds__(TL ? kTableBlock : kBlock) void k_force(Buffers b, int p, int q, int64_t n_slots,
-                                                                      PotArgs P, double dt, md_state st)
-{
-    constexpr bool WSUM = EN == 4;
-    constexpr int ENERGY = WSUM ? 1 : EN;
-    extern __shared__ __align__(16) unsigned char smem[];
-    const Tabs<R> T = tables<R>(b);
-    const R* tf = T.force;
-    const R* te = T.energy;
-    if (EV != EV_KNOTS && (SINGLE || TL)) {
-        const int nf = (SINGLE ? 1 : P.ns * P.ns) * P.nbt * force_stride(EV);
-        R* s = reinterpret_cast<R*>(smem);
-        lds_fill(s, tf, nf);
-        if (ENERGY == 1) lds_fill(s + nf, te, (SINGLE ? 1 : P.ns * P.ns) * P.nbt * value_stride(EV));
-        __syncthreads();
-        tf = s;
-        te = s + nf;
-    }
-    const int64_t t = global_thread();
-    if (t >= n_slots) return;
-    const DevReplica& Rp = b.reps[uniform(b.rep_of_wave[t / kWave])];
-    // slots past the replica's atoms: none in energy-sum mode, whose wavefront
-    // sums need every lane (those lanes add zeros)
-    const bool pad = t - Rp.slot_off >= Rp.n_atoms;
-    if (pad && !WSUM) return;
-    const Box bx = load_box(Rp);
-    const DevPotential& G = *b.pot;
-    const double4* __restrict__ pos = b.pos[p];
-    const int4* __restrict__ rec = b.rec[1];
-    const int32_t* __restrict__ nbr = b.nbr;
-    const double4 pi = pos[t];
-    const int4 qi = CMP ? rec[t] : make_int4(0, 0, 0, 0);
-    const int4 qb = compact_base(qi);
-    const __amdgpu_buffer_rsrc_t rs = record_rsrc(b.rec[1], n_slots);
-    const uint8_t ti = b.type[q][t];
-    const int si = ti & 0x3F;
-    const bool rigid_i = ti & kRigidBit;
-    const int n = pad ? 0 : b.ncount[t];
-    const R fpi = CMP ? (R)__int_as_float(qi.w) : (R)pi.w;
-    PairAcc A;
-    constexpr int GR = NCH >= kChunk ? NCH / kChunk : 1;  // list groups per iteration
-    constexpr int SUB = NCH >= kChunk ? 1 : kChunk / NCH;  // record batches per group
-    static_assert(kChunk == 4 && NCH * SUB == kChunk * GR, "one int4 list load per four entries");
-    for (int k0 = 0; k0 < n; k0 += kChunk * GR) {
-        int v[kChunk * GR];
-#pragma unroll
-        for (int g = 0; g < GR; ++g) {  // 16-byte loads of four entries; groups past cap are padding
-            const int4 v4 = reinterpret_cast<const int4*>(nbr)[(int64_t)((k0 >> 2) + g) * n_slots + t];
-            v[4 * g] = v4.x;
-            v[4 * g + 1] = v4.y;
-            v[4 * g + 2] = v4.z;
-            v[4 * g + 3] = v4.w;
-        }
-        uint32_t tv[GR];  // neighbour type bytes of the groups (several species)
-#pragma unroll
-        for (int g = 0; g < GR; ++g)
-            tv[g] = SINGLE ? 0u : reinterpret_cast<const uint32_t*>(b.ntype)[(int64_t)((k0 >> 2) + g) * n_slots + t];
-#pragma unroll
-        for (int sb = 0; sb < SUB; ++sb) {
-            const int kb = k0 + sb * NCH;
-            if (kb >= n) break;
-            int e[NCH];
-            double4 ps[NCH];
-            int4 qs[NCH];
-#pragma unroll
-            for (int u = 0; u < NCH; ++u) {
-                e[u] = kb + u < n ? v[sb * NCH + u] : (int)t;
-                if (CMP) qs[u] = record_load(rs, e[u] & kIndexMask);
-                else ps[u] = pos[e[u] & kIndexMask];
-            }
-#pragma unroll
-            for (int u = 0; u < NCH; ++u) {
-                if (kb + u >= n) break;
-                const int code = ((unsigned)e[u] >> kIndexBits) & kCodeMask;
-                double dx, dy, dz;
-                R fpj;
-                if (CMP) {
-                    compact_delta<CMP>(Rp, qb, qs[u], code, dx, dy, dz);
-                    fpj = (R)__int_as_float(qs[u].w);
-                } else {
-                    dx = ps[u].x - pi.x;
-                    dy = ps[u].y - pi.y;
-                    dz = ps[u].z - pi.z;
-                    if (code) apply_shift(bx, code, dx, dy, dz);
-                    fpj = (R)ps[u].w;
-                }
-                const double r2 = fma(dx, dx, fma(dy, dy, dz * dz));
-                if (!(r2 < P.rc2)) continue;
-                const double ri = inv_dist<R>(r2);
-                const double r = r2 * ri;
-                // one species: j's type byte matters only for the virial of a rigid
-                // atom i (pairs of two rigid atoms stay out of it)
-                const int ku = sb * NCH + u;  // entry within the groups loaded
-                const uint8_t tj = !SINGLE ? (uint8_t)(tv[ku >> 2] >> (8 * (ku & 3)))
-                                           : (ENERGY == 1 && rigid_i) ? b.type[q][e[u] & kIndexMask] : 0;
-                R g, phi;
-                pair_terms<R, SINGLE, NPK, NDK, EV, ENERGY>(P, G, tf, te, si, tj & 0x3F, r, fpi, fpj, g, phi);
-                accumulate<ENERGY>(A, (double)g * ri, dx, dy, dz, (double)phi, rigid_i && (tj & kRigidBit));
-            }
-        }
-    }
-    double wv[kEnergyTerms] = {};
-    if (!pad) atom_epilogue<SINGLE, ENERGY, CLOSE, OPEN, WRITEBACK, WSUM>(b, p, q, t, n_slots, Rp, P, G, dt, st, pi, ti,
-                                                                      A, wv);
-    if (WSUM) wave_sum_terms(b, t, wv);
-    if (CMP && OPEN && !pad) {
-        // the compact record of the drifted position, for the next density pass
-        const int4 c4 = b.cellxyz[t];
-        const int c[3] = {c4.x, c4.y, c4.z};
-        const double3 xn = load_xyz(b.pos[p ^ 1], t);
-        int4 rq;
-        if (!compact_coords<CMP>(Rp, c, xn.x, xn.y, xn.z, rq)) atomicAdd(&b.flags[F_COMPACT], 1);
-        b.rec[0][t] = rq;
-    }
 }
 
 // Per-replica totals of the per-atom energy terms, in two stages with a fixed
@@ -991,156 +696,6 @@ __global__ void k_gear_correct(Buffers b, int p, int q, int64_t n_slots, PotArgs
     }
 }
 
-// ---------------------------------------------------------------------------
-// Half-list variant (MD_NBR_HALF_ATOMIC): the comparison form in which every
-// unordered pair is evaluated once, by its lower slot, and the partner's share
-// goes to memory with FP64 atomics; the paper's own OpenMP code resolves the
-// same write conflict with link-cell locks (section "OpenMP Parallelisation").
-// Density: rho_i and rho_j both receive their term; the embedding then runs as
-// its own pass.  Forces: f_i += s d, f_j -= s d; pair energies split in halves;
-// the virial counts every pair once.  Integration follows as a separate pass.
-
-// Density pass, half list: accumulates into rhalf (zeroed beforehand).
-template <typename R, bool SINGLE, int NPK, int NDK, int EV>
-__global__ __launch_bounds__(kBlock) void k_density_half(Buffers b, int p, int q, int64_t n_slots, PotArgs P)
-{
-    extern __shared__ __align__(16) unsigned char smem[];
-    const R* tab = tables<R>(b).dens;
-    if (EV != EV_KNOTS && SINGLE) {
-        R* s = reinterpret_cast<R*>(smem);
-        lds_fill(s, tab, P.nbt * value_stride(EV));
-        __syncthreads();
-        tab = s;
-    }
-    const int64_t t = global_thread();
-    if (t >= n_slots) return;
-    const DevReplica& Rp = b.reps[uniform(b.rep_of_wave[t / kWave])];
-    if (t - Rp.slot_off >= Rp.n_atoms) return;
-    const Box bx = load_box(Rp);
-    const DevPotential& G = *b.pot;
-    const double4* __restrict__ pos = b.pos[p];
-    const int32_t* __restrict__ nbr = b.nbr;
-    const double3 xi = load_xyz(pos, t);
-    const int si = b.type[q][t] & 0x3F;
-    const int n = b.ncount[t];
-    double rho = 0.0;
-    for (int k = 0; k < n; ++k) {
-        const int e = nbr[nbr_at(k, t, n_slots)];
-        const int j = e & kIndexMask;
-        const double3 xj = load_xyz(pos, j);
-        double dx = xj.x - xi.x, dy = xj.y - xi.y, dz = xj.z - xi.z;
-        const int code = ((unsigned)e >> kIndexBits) & kCodeMask;
-        if (code) apply_shift(bx, code, dx, dy, dz);
-        const double r2 = dx * dx + dy * dy + dz * dz;
-        if (!(r2 < P.rc2)) continue;
-        const double r = r2 * inv_dist<R>(r2);
-        const int sj = SINGLE ? 0 : (b.type[q][j] & 0x3F);
-        const R to_i = density_term<R, SINGLE, NDK, EV>(P, G, tab, si, sj, r);
-        const R to_j = SINGLE ? to_i : density_term<R, SINGLE, NDK, EV>(P, G, tab, sj, si, r);
-        rho += (double)to_i;
-        atomicAdd(&b.rhalf[j], (double)to_j);
-    }
-    atomicAdd(&b.rhalf[t], rho);
-}
-
-// Embedding after the half-list density pass: F_i, F'_i from rho_i.
-template <bool SINGLE>
-__global__ void k_embed_half(Buffers b, int p, int q, int64_t n_slots, PotArgs P, int energy)
-{
-    const int64_t t = global_thread();
-    if (t >= n_slots) return;
-    const DevReplica& Rp = b.reps[uniform(b.rep_of_wave[t / kWave])];
-    if (t - Rp.slot_off >= Rp.n_atoms) return;
-    const DevPotential& G = *b.pot;
-    const int si = b.type[q][t] & 0x3F;
-    double F, dF;
-    embed(SINGLE ? P.emb_c : G.emb_c[si], b.rhalf[t], F, dF);
-    reinterpret_cast<double*>(b.pos[p] + t)[3] = dF;
-    if (energy) b.femb[t] = F;
-}
-
-// Force pass, half list: forces and pair energies into fhalf / ehalf (zeroed
-// beforehand); the virial of the pairs an atom owns into its energy slots.
-template <typename R, bool SINGLE, int NPK, int NDK, int EV, bool ENERGY>
-__global__ __launch_bounds__(kBlock) void k_force_half(Buffers b, int p, int q, int64_t n_slots, PotArgs P)
-{
-    extern __shared__ __align__(16) unsigned char smem[];
-    const Tabs<R> T = tables<R>(b);
-    const R* tf = T.force;
-    const R* te = T.energy;
-    if (EV != EV_KNOTS && SINGLE) {
-        R* s = reinterpret_cast<R*>(smem);
-        lds_fill(s, tf, P.nbt * force_stride(EV));
-        if (ENERGY == 1) lds_fill(s + P.nbt * force_stride(EV), te, P.nbt * value_stride(EV));
-        __syncthreads();
-        tf = s;
-        te = s + P.nbt * force_stride(EV);
-    }
-    const int64_t t = global_thread();
-    if (t >= n_slots) return;
-    const DevReplica& Rp = b.reps[uniform(b.rep_of_wave[t / kWave])];
-    if (t - Rp.slot_off >= Rp.n_atoms) return;
-    const Box bx = load_box(Rp);
-    const DevPotential& G = *b.pot;
-    const double4* __restrict__ pos = b.pos[p];
-    const int32_t* __restrict__ nbr = b.nbr;
-    const double4 pi = pos[t];
-    const uint8_t ti = b.type[q][t];
-    const int si = ti & 0x3F;
-    const bool rigid_i = ti & kRigidBit;
-    const int n = b.ncount[t];
-    PairAcc A;
-    for (int k = 0; k < n; ++k) {
-        const int e = nbr[nbr_at(k, t, n_slots)];
-        const int j = e & kIndexMask;
-        const double4 pj = pos[j];
-        double dx = pj.x - pi.x, dy = pj.y - pi.y, dz = pj.z - pi.z;
-        const int code = ((unsigned)e >> kIndexBits) & kCodeMask;
-        if (code) apply_shift(bx, code, dx, dy, dz);
-        const double r2 = dx * dx + dy * dy + dz * dz;
-        if (!(r2 < P.rc2)) continue;
-        const double ri = inv_dist<R>(r2);
-        const double r = r2 * ri;
-        const uint8_t tj = (!SINGLE || ENERGY) ? b.type[q][j] : 0;
-        R g, phi;
-        pair_terms<R, SINGLE, NPK, NDK, EV, ENERGY>(P, G, tf, te, si, tj & 0x3F, r, (R)pi.w, (R)pj.w, g, phi);
-        const double s = (double)g * ri;
-        accumulate<ENERGY>(A, s, dx, dy, dz, (double)phi, rigid_i && (tj & kRigidBit));
-        atomicAdd(&b.fhalf[0][j], -s * dx);
-        atomicAdd(&b.fhalf[1][j], -s * dy);
-        atomicAdd(&b.fhalf[2][j], -s * dz);
-        if (ENERGY) atomicAdd(&b.ehalf[j], 0.5 * (double)phi);
-    }
-#pragma unroll
-    for (int a = 0; a < 3; ++a) atomicAdd(&b.fhalf[a][t], A.f[a]);
-    if (ENERGY) {
-        atomicAdd(&b.ehalf[t], 0.5 * A.epair);
-#pragma unroll
-        for (int k = 0; k < 6; ++k) b.eslot[(int64_t)(E_W0 + k) * n_slots + t] = A.w[k];
-    }
-}
-
-// Velocity Verlet and energy terms after the half-list force pass.
-template <bool SINGLE, bool ENERGY, bool CLOSE, bool OPEN, bool WRITEBACK>
-__global__ void k_integrate_half(Buffers b, int p, int q, int64_t n_slots, PotArgs P, double dt, md_state st)
-{
-    const int64_t t = global_thread();
-    if (t >= n_slots) return;
-    const DevReplica& Rp = b.reps[uniform(b.rep_of_wave[t / kWave])];
-    if (t - Rp.slot_off >= Rp.n_atoms) return;
-    const DevPotential& G = *b.pot;
-    PairAcc A;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) A.f[a] = b.fhalf[a][t];
-    if (ENERGY) {
-        A.epair = 2.0 * b.ehalf[t];
-#pragma unroll
-        for (int k = 0; k < 6; ++k) A.w[k] = b.eslot[(int64_t)(E_W0 + k) * n_slots + t];
-    }
-    atom_epilogue<SINGLE, ENERGY, CLOSE, OPEN, WRITEBACK>(b, p, q, t, n_slots, Rp, P, G, dt, st, b.pos[p][t],
-                                                         b.type[q][t], A);
-}
-
 }  // namespace
 
 // ---------------------------------------------------------------------------
@@ -1149,6 +704,12 @@ void launch_fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t s)
 {
     if (n <= 0) return;
     hipLaunchKernelGGL(k_fill_i32, dim3(blocks_for(n)), dim3(kBlock), 0, s, p, v, n);
+}
+
+void launch_fill_f64(double* p, double v, int64_t n, hipStream_t s)
+{
+    if (n <= 0) return;
+    hipLaunchKernelGGL(k_fill_f64, dim3(blocks_for(n)), dim3(kBlock), 0, s, p, v, n);
 }
 
 void launch_init_slots(const Buffers& b, int q, const md_state& st, const KernelShape& k, hipStream_t s)
@@ -1169,252 +730,36 @@ void launch_compact_records(const Buffers& b, int p, const KernelShape& k, hipSt
     hipLaunchKernelGGL(k_compact_records, dim3(blocks_for(k.n_slots)), dim3(kBlock), 0, s, b, p, k.n_slots);
 }
 
-template <typename R, bool S, int NP, int ND, int EV, int CMP, bool TL>
-static void density_chunked(const Buffers& b, int p, int q, const KernelShape& k, const PotArgs& P, int energy,
-                            size_t lds, hipStream_t s)
-{
-    const int block = TL ? kTableBlock : kBlock;
-    const dim3 grid((unsigned)((k.n_slots + block - 1) / block));
-    if (k.nchunk == 2)
-        hipLaunchKernelGGL((k_density<R, S, NP, ND, EV, CMP, 2, TL>), grid, dim3(block), lds, s, b, p, q, k.n_slots,
-                           P, energy);
-    else if (k.nchunk == 8)
-        hipLaunchKernelGGL((k_density<R, S, NP, ND, EV, CMP, 8, TL>), grid, dim3(block), lds, s, b, p, q, k.n_slots,
-                           P, energy);
-    else
-        hipLaunchKernelGGL((k_density<R, S, NP, ND, EV, CMP, 4, TL>), grid, dim3(block), lds, s, b, p, q, k.n_slots,
-                           P, energy);
-}
-
-template <typename R, bool S, int NP, int ND, int EV, int CMP>
-static void density_tables(const Buffers& b, int p, int q, const KernelShape& k, const PotArgs& P, int energy,
-                           hipStream_t s)
-{
-    // tables in LDS: always for one species, for several when they fit
-    const size_t bytes = EV != EV_KNOTS ? (size_t)(S ? 1 : P.ns * P.ns) * P.nbt * value_stride(EV) * sizeof(R) : 0;
-    if constexpr (!S && EV != EV_KNOTS) {
-        if (bytes <= (size_t)k.lds_limit) {
-            density_chunked<R, S, NP, ND, EV, CMP, true>(b, p, q, k, P, energy, bytes, s);
-            return;
-        }
-    }
-    density_chunked<R, S, NP, ND, EV, CMP, false>(b, p, q, k, P, energy, S ? bytes : 0, s);
-}
-
-template <typename R, bool S, int NP, int ND, int EV>
-static void density_variant(const Buffers& b, int p, int q, const KernelShape& k, const PotArgs& P, int energy,
-                            hipStream_t s)
-{
-    if (k.compact == 2) density_tables<R, S, NP, ND, EV, 2>(b, p, q, k, P, energy, s);
-    else if (k.compact) density_tables<R, S, NP, ND, EV, 1>(b, p, q, k, P, energy, s);
-    else density_tables<R, S, NP, ND, EV, 0>(b, p, q, k, P, energy, s);
-}
-
-template <typename R, bool S, int NP, int ND, int EV>
-static void density_half_variant(const Buffers& b, int p, int q, const KernelShape& k, const PotArgs& P, int energy,
-                                 hipStream_t s)
-{
-    const size_t lds = (EV != EV_KNOTS && S) ? (size_t)P.nbt * value_stride(EV) * sizeof(R) : 0;
-    const dim3 grid(blocks_for(k.n_slots));
-    hipLaunchKernelGGL(k_fill_f64, grid, dim3(kBlock), 0, s, b.rhalf, 0.0, k.n_slots);
-    hipLaunchKernelGGL((k_density_half<R, S, NP, ND, EV>), grid, dim3(kBlock), lds, s, b, p, q, k.n_slots, P);
-    hipLaunchKernelGGL((k_embed_half<S>), grid, dim3(kBlock), 0, s, b, p, q, k.n_slots, P, energy);
-}
-
+// Global-gather kernels: instantiated in kernels_global_*.hip.
 template <typename R, bool S>
-static void density_dispatch(const Buffers& b, int p, int q, const KernelShape& k, const PotArgs& P, int half_list,
-                             int energy, hipStream_t s)
-{
-    // the term-by-term knot sums are FP64 only (the runtime refuses them in mixed precision)
-    constexpr bool knots = sizeof(R) == 8;
-    if (half_list) {
-        if (k.table == 2) density_half_variant<R, S, 8, 8, EV_SPLIT>(b, p, q, k, P, energy, s);
-        else if (k.table || !knots) density_half_variant<R, S, 8, 8, EV_TABLE>(b, p, q, k, P, energy, s);
-        else if constexpr (knots) {
-            if (k.ndk == 2) density_half_variant<R, S, 6, 2, EV_KNOTS>(b, p, q, k, P, energy, s);  // density knots only
-            else density_half_variant<R, S, 8, 8, EV_KNOTS>(b, p, q, k, P, energy, s);
-        }
-        return;
-    }
-    if (k.table == 2) density_variant<R, S, 8, 8, EV_SPLIT>(b, p, q, k, P, energy, s);
-    else if (k.table || !knots) density_variant<R, S, 8, 8, EV_TABLE>(b, p, q, k, P, energy, s);
-    else if constexpr (knots) {
-        if (k.ndk == 2) density_variant<R, S, 6, 2, EV_KNOTS>(b, p, q, k, P, energy, s);  // density knots only
-        else density_variant<R, S, 8, 8, EV_KNOTS>(b, p, q, k, P, energy, s);
-    }
-}
+void density_of(const Buffers& b, int p, int q, const KernelShape& k, const PotArgs& P, int half_list, int energy,
+                hipStream_t s);
+template <typename R, bool S>
+void force_of(const Buffers& b, int p, int q, const KernelShape& k, const PotArgs& P, int half_list, ForceFlags fl,
+              double dt_fs, const md_state& st, hipStream_t s);
 
 void launch_density(const Buffers& b, int p, int q, const KernelShape& k, const PotArgs& P, int precision,
                     int half_list, int energy, hipStream_t s)
 {
     const bool one = P.ns == 1;
     if (precision == MD_MIXED) {
-        if (one) density_dispatch<float, true>(b, p, q, k, P, half_list, energy, s);
-        else density_dispatch<float, false>(b, p, q, k, P, half_list, energy, s);
+        if (one) density_of<float, true>(b, p, q, k, P, half_list, energy, s);
+        else density_of<float, false>(b, p, q, k, P, half_list, energy, s);
     } else {
-        if (one) density_dispatch<double, true>(b, p, q, k, P, half_list, energy, s);
-        else density_dispatch<double, false>(b, p, q, k, P, half_list, energy, s);
+        if (one) density_of<double, true>(b, p, q, k, P, half_list, energy, s);
+        else density_of<double, false>(b, p, q, k, P, half_list, energy, s);
     }
 }
-
-// The neighbour chunk applies to the velocity-Verlet step kernels (with and
-// without energies) and to the plain force pass the autotuner times; the other
-// variants run once per call or per barostat step.
-template <typename R, bool S, int NP, int ND, int EV, int E, bool C, bool O, bool W, int CMP, bool TL>
-static void force_chunked(const Buffers& b, int p, int q, const KernelShape& k, const PotArgs& P, double dt_fs,
-                          const md_state& st, size_t lds, hipStream_t s)
-{
-    const int block = TL ? kTableBlock : kBlock;
-    const dim3 grid((unsigned)((k.n_slots + block - 1) / block));
-    constexpr bool step = ((E == 0 || E == 1 || E == 4) && C && O && !W) || (E == 0 && !C && !O && !W);
-    if constexpr (step) {
-        if (k.nchunk == 2) {
-            hipLaunchKernelGGL((k_force<R, S, NP, ND, EV, E, C, O, W, CMP, 2, TL>), grid, dim3(block), lds, s, b, p,
-                               q, k.n_slots, P, dt_fs, st);
-            return;
-        }
-        if (k.nchunk == 8) {
-            hipLaunchKernelGGL((k_force<R, S, NP, ND, EV, E, C, O, W, CMP, 8, TL>), grid, dim3(block), lds, s, b, p,
-                               q, k.n_slots, P, dt_fs, st);
-            return;
-        }
-    }
-    hipLaunchKernelGGL((k_force<R, S, NP, ND, EV, E, C, O, W, CMP, 4, TL>), grid, dim3(block), lds, s, b, p, q,
-                       k.n_slots, P, dt_fs, st);
-}
-
-template <typename R, bool S, int NP, int ND, int EV, int E, bool C, bool O, bool W, int CMP>
-static void force_tables(const Buffers& b, int p, int q, const KernelShape& k, const PotArgs& P, double dt_fs,
-                         const md_state& st, hipStream_t s)
-{
-    // tables in LDS: always for one species, for several when they fit
-    const size_t bytes = EV != EV_KNOTS ? (size_t)(S ? 1 : P.ns * P.ns) * P.nbt *
-                                              (force_stride(EV) + (E == 1 || E == 4 ? value_stride(EV) : 0)) *
-                                              sizeof(R)
-                                        : 0;
-    if constexpr (!S && EV != EV_KNOTS) {
-        if (bytes <= (size_t)k.lds_limit) {
-            force_chunked<R, S, NP, ND, EV, E, C, O, W, CMP, true>(b, p, q, k, P, dt_fs, st, bytes, s);
-            return;
-        }
-    }
-    force_chunked<R, S, NP, ND, EV, E, C, O, W, CMP, false>(b, p, q, k, P, dt_fs, st, S ? bytes : 0, s);
-}
-
-template <typename R, bool S, int NP, int ND, int EV, int E, bool C, bool O, bool W>
-static void force_launch(const Buffers& b, int p, int q, const KernelShape& k, const PotArgs& P, double dt_fs,
-                         const md_state& st, hipStream_t s)
-{
-    if (k.compact == 2) force_tables<R, S, NP, ND, EV, E, C, O, W, 2>(b, p, q, k, P, dt_fs, st, s);
-    else if (k.compact) force_tables<R, S, NP, ND, EV, E, C, O, W, 1>(b, p, q, k, P, dt_fs, st, s);
-    else force_tables<R, S, NP, ND, EV, E, C, O, W, 0>(b, p, q, k, P, dt_fs, st, s);
-}
-
-template <typename R, bool S, int NP, int ND, int EV>
-static void force_variant(const Buffers& b, int p, int q, const KernelShape& k, const PotArgs& P, ForceFlags fl,
-                          double dt_fs, const md_state& st, hipStream_t s)
-{
-    if (!fl.close && !fl.open) {
-        if (!fl.writeback && fl.energy == 3)  // full-matrix barostat: the whole virial tensor, forces kept
-            force_launch<R, S, NP, ND, EV, 3, false, false, false>(b, p, q, k, P, dt_fs, st, s);
-        else if (!fl.writeback && fl.energy)  // barostat: the stress of the starting state, forces kept
-            force_launch<R, S, NP, ND, EV, 2, false, false, false>(b, p, q, k, P, dt_fs, st, s);
-        else if (!fl.writeback) force_launch<R, S, NP, ND, EV, false, false, false, false>(b, p, q, k, P, dt_fs, st, s);
-        else if (fl.energy == 4) force_launch<R, S, NP, ND, EV, 4, false, false, true>(b, p, q, k, P, dt_fs, st, s);
-        else if (fl.energy) force_launch<R, S, NP, ND, EV, true, false, false, true>(b, p, q, k, P, dt_fs, st, s);
-        else force_launch<R, S, NP, ND, EV, false, false, false, true>(b, p, q, k, P, dt_fs, st, s);
-    } else if (!fl.close && fl.open) {
-        force_launch<R, S, NP, ND, EV, false, false, true, false>(b, p, q, k, P, dt_fs, st, s);
-    } else if (fl.close && fl.open) {
-        if (fl.energy == 4)  // per-step energies, summed per wavefront
-            force_launch<R, S, NP, ND, EV, 4, true, true, false>(b, p, q, k, P, dt_fs, st, s);
-        else if (fl.energy)  // per-step energies
-            force_launch<R, S, NP, ND, EV, true, true, true, false>(b, p, q, k, P, dt_fs, st, s);
-        else force_launch<R, S, NP, ND, EV, false, true, true, false>(b, p, q, k, P, dt_fs, st, s);
-    } else if (!fl.writeback && fl.energy == 3) {  // full-matrix barostat: closing kick, virial tensor
-        force_launch<R, S, NP, ND, EV, 3, true, false, false>(b, p, q, k, P, dt_fs, st, s);
-    } else if (!fl.writeback && fl.energy) {  // barostat: closing kick with the stress, forces kept
-        force_launch<R, S, NP, ND, EV, 2, true, false, false>(b, p, q, k, P, dt_fs, st, s);
-    } else if (!fl.writeback) {
-        force_launch<R, S, NP, ND, EV, false, true, false, false>(b, p, q, k, P, dt_fs, st, s);
-    } else if (fl.energy == 4) {  // the last step of a velocity-Verlet call
-        force_launch<R, S, NP, ND, EV, 4, true, false, true>(b, p, q, k, P, dt_fs, st, s);
-    } else {
-        force_launch<R, S, NP, ND, EV, true, true, false, true>(b, p, q, k, P, dt_fs, st, s);
-    }
-}
-
-template <bool S, bool E, bool C, bool O, bool W>
-static void integrate_half(const Buffers& b, int p, int q, const KernelShape& k, const PotArgs& P, double dt_fs,
-                           const md_state& st, hipStream_t s)
-{
-    hipLaunchKernelGGL((k_integrate_half<S, E, C, O, W>), dim3(blocks_for(k.n_slots)), dim3(kBlock), 0, s, b, p, q,
-                       k.n_slots, P, dt_fs, st);
-}
-
-template <typename R, bool S, int NP, int ND, int EV>
-static void force_half_variant(const Buffers& b, int p, int q, const KernelShape& k, const PotArgs& P, ForceFlags fl,
-                               double dt_fs, const md_state& st, hipStream_t s)
-{
-    const dim3 grid(blocks_for(k.n_slots));
-    for (int a = 0; a < 3; ++a) hipLaunchKernelGGL(k_fill_f64, grid, dim3(kBlock), 0, s, b.fhalf[a], 0.0, k.n_slots);
-    if (fl.energy) hipLaunchKernelGGL(k_fill_f64, grid, dim3(kBlock), 0, s, b.ehalf, 0.0, k.n_slots);
-    const size_t lds =
-        (EV != EV_KNOTS && S) ? (size_t)P.nbt * (force_stride(EV) + (fl.energy ? value_stride(EV) : 0)) * sizeof(R) : 0;
-    if (fl.energy)
-        hipLaunchKernelGGL((k_force_half<R, S, NP, ND, EV, true>), grid, dim3(kBlock), lds, s, b, p, q, k.n_slots, P);
-    else
-        hipLaunchKernelGGL((k_force_half<R, S, NP, ND, EV, false>), grid, dim3(kBlock), lds, s, b, p, q, k.n_slots, P);
-    if (!fl.close && !fl.open) {
-        if (!fl.writeback) integrate_half<S, false, false, false, false>(b, p, q, k, P, dt_fs, st, s);
-        else if (fl.energy) integrate_half<S, true, false, false, true>(b, p, q, k, P, dt_fs, st, s);
-        else integrate_half<S, false, false, false, true>(b, p, q, k, P, dt_fs, st, s);
-    } else if (!fl.close && fl.open) {
-        integrate_half<S, false, false, true, false>(b, p, q, k, P, dt_fs, st, s);
-    } else if (fl.close && fl.open) {
-        if (fl.energy) integrate_half<S, true, true, true, false>(b, p, q, k, P, dt_fs, st, s);
-        else integrate_half<S, false, true, true, false>(b, p, q, k, P, dt_fs, st, s);
-    } else if (!fl.writeback) {
-        integrate_half<S, false, true, false, false>(b, p, q, k, P, dt_fs, st, s);
-    } else {
-        integrate_half<S, true, true, false, true>(b, p, q, k, P, dt_fs, st, s);
-    }
-}
-
-template <typename R, bool S>
-static void force_dispatch(const Buffers& b, int p, int q, const KernelShape& k, const PotArgs& P, int half_list,
-                           ForceFlags fl, double dt_fs, const md_state& st, hipStream_t s)
-{
-    constexpr bool knots = sizeof(R) == 8;  // knot sums: FP64 only
-    if (half_list) {
-        if (k.table == 2) force_half_variant<R, S, 8, 8, EV_SPLIT>(b, p, q, k, P, fl, dt_fs, st, s);
-        else if (k.table || !knots) force_half_variant<R, S, 8, 8, EV_TABLE>(b, p, q, k, P, fl, dt_fs, st, s);
-        else if constexpr (knots) {
-            if (k.npk == 6 && k.ndk == 2) force_half_variant<R, S, 6, 2, EV_KNOTS>(b, p, q, k, P, fl, dt_fs, st, s);
-            else if (k.npk <= 8 && k.ndk <= 8) force_half_variant<R, S, 8, 8, EV_KNOTS>(b, p, q, k, P, fl, dt_fs, st, s);
-            else if constexpr (S) force_half_variant<R, S, 16, 4, EV_KNOTS>(b, p, q, k, P, fl, dt_fs, st, s);
-        }
-        return;
-    }
-    if (k.table == 2) force_variant<R, S, 8, 8, EV_SPLIT>(b, p, q, k, P, fl, dt_fs, st, s);
-    else if (k.table || !knots) force_variant<R, S, 8, 8, EV_TABLE>(b, p, q, k, P, fl, dt_fs, st, s);
-    else if constexpr (knots) {
-        if (k.npk == 6 && k.ndk == 2) force_variant<R, S, 6, 2, EV_KNOTS>(b, p, q, k, P, fl, dt_fs, st, s);
-        else if (k.npk <= 8 && k.ndk <= 8) force_variant<R, S, 8, 8, EV_KNOTS>(b, p, q, k, P, fl, dt_fs, st, s);
-        else if constexpr (S) force_variant<R, S, 16, 4, EV_KNOTS>(b, p, q, k, P, fl, dt_fs, st, s);
-    }
-}
-
 void launch_force(const Buffers& b, int p, int q, const KernelShape& k, const PotArgs& P, int precision,
                   int half_list, ForceFlags fl, double dt_fs, const md_state& st, hipStream_t s)
 {
     const bool one = P.ns == 1;
     if (precision == MD_MIXED) {
-        if (one) force_dispatch<float, true>(b, p, q, k, P, half_list, fl, dt_fs, st, s);
-        else force_dispatch<float, false>(b, p, q, k, P, half_list, fl, dt_fs, st, s);
+        if (one) force_of<float, true>(b, p, q, k, P, half_list, fl, dt_fs, st, s);
+        else force_of<float, false>(b, p, q, k, P, half_list, fl, dt_fs, st, s);
     } else {
-        if (one) force_dispatch<double, true>(b, p, q, k, P, half_list, fl, dt_fs, st, s);
-        else force_dispatch<double, false>(b, p, q, k, P, half_list, fl, dt_fs, st, s);
+        if (one) force_of<double, true>(b, p, q, k, P, half_list, fl, dt_fs, st, s);
+        else force_of<double, false>(b, p, q, k, P, half_list, fl, dt_fs, st, s);
     }
 }
 

@@ -23,7 +23,9 @@ constexpr int kWave = 64;       // CDNA wavefront
 constexpr int kBlock = 256;     // threads per workgroup (4 waves)
 constexpr int kCandTable = 512; // list build: candidates one wave's LDS table holds
 constexpr int kTableBlock = 1024;  // global kernels with several species' tables in LDS
+constexpr int kSplit = 8;       // waves sharing the neighbours of 64 atoms (small systems)
 constexpr int kEnergySlots = 12;  // per-wave partial record, see EnergyIndex
+constexpr int kSimds = 1024;    // MI355X: 256 CUs of 4 SIMDs
 constexpr int kNumXcd = 8;      // MI355X: 8 accelerator dies, one L2 each
 
 enum EnergyIndex { E_PE = 0, E_KE = 1, E_W0 = 2, E_PW = 8, E_NONFINITE = 9 };
@@ -253,12 +255,14 @@ struct KernelShape {
     int32_t list_types; // the global list also stores its entries' type bytes (several species)
     int32_t split_list; // the global list marks its inner entries (FP64: the density pass then
                         // gathers only those)
+    int32_t split;     // 1 = the global kernels deal each atom's neighbours to kSplit waves
     int32_t chunked;  // 1 = per-replica sums of the thermostat and barostat start with
                       // per-chunk sums (some replica spans more than kChunkedSumWaves waves)
 };
 
 // Launchers (kernels.hip).  All enqueue on `s`.
 void launch_fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t s);
+void launch_fill_f64(double* p, double v, int64_t n, hipStream_t s);
 void launch_init_slots(const Buffers& b, int q, const md_state& st, const KernelShape& k, hipStream_t s);
 void launch_load_state(const Buffers& b, int p, int q, const md_state& st, const KernelShape& k,
                        hipStream_t s);

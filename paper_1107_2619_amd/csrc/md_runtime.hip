@@ -204,6 +204,8 @@ KernelShape shape(const md_ctx* c)
     k.chunked = c->chunked_sums ? 1 : 0;
     k.lds_limit = c->lds_limit;
     k.nchunk = c->nchunk;
+    // few atoms: up to two one-thread wavefronts per SIMD (see kernels_global.h)
+    k.split = c->Np <= (int64_t)2 * kSimds * kWave;
     k.list_types = c->single ? 0 : 1;
     // FP64 density passes gather 24 bytes per neighbour and gain from skipping
     // the outer entries; the 16-byte compact records of mixed precision do not
