@@ -201,7 +201,7 @@ __global__ void k_sort_cells(Buffers b, int q, int64_t n_slots, const int32_t* _
 }
 
 // Rebuild stage 5: gather the whole atom state into the new slot order.
-__device__ __forceinline__ void gather_slot(const Buffers& b, int p, int q, int64_t u)
+__device__ __forceinline__ void gather_slot(const Buffers& b, int p, int q, int64_t u, int compact)
 {
     const DevReplica& R = b.reps[uniform(b.rep_of_wave[u / kWave])];
     const int pn = p ^ 1, qn = q ^ 1;
@@ -240,6 +240,17 @@ __device__ __forceinline__ void gather_slot(const Buffers& b, int p, int q, int6
         const double4 x4 = make_double4(xw[0], xw[1], xw[2], 0.0);
         b.pos[pn][u] = x4;
         b.xbuild[u] = x4;
+        if (compact) {
+            // the slot's link cell and its compact record (here, where every lane
+            // holds an atom, and not in the list kernel, whose wavefronts own a
+            // handful each)
+            const int cpk = b.cell_coord[b.cell_of[t]];
+            const int c[3] = {cpk & 1023, (cpk >> 10) & 1023, cpk >> 20};
+            int4 rq;
+            if (!compact_coords(R, c, xw[0], xw[1], xw[2], rq)) atomicAdd(&b.flags[F_COMPACT], 1);
+            b.cellxyz[u] = make_int4(c[0], c[1], c[2], 0);
+            b.rec[0][u] = rq;
+        }
 #pragma unroll
         for (int a = 0; a < 3; ++a) b.vel[qn][a][u] = b.vel[q][a][t];
         b.id[qn][u] = b.id[q][t];
@@ -274,12 +285,12 @@ __device__ __forceinline__ void gather_slot(const Buffers& b, int p, int q, int6
     }
 }
 
-__global__ void k_gather(Buffers b, int p, int q, int64_t n_slots, const int32_t* __restrict__ gate)
+__global__ void k_gather(Buffers b, int p, int q, int64_t n_slots, int compact, const int32_t* __restrict__ gate)
 {
     if (gate && gate[0] == 0) return;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t u = global_thread(); u < n_slots; u += stride)
-        if (!replica_kept(b, gate, u)) gather_slot(b, p, q, u);
+        if (!replica_kept(b, gate, u)) gather_slot(b, p, q, u, compact);
 }
 
 // Verlet list from the link cells (paper, "The Neighbourlist calculation":
@@ -287,14 +298,14 @@ __global__ void k_gather(Buffers b, int p, int q, int64_t n_slots, const int32_t
 // cell.  The up to 27 adjacent cells (fewer on free faces; on a periodic axis
 // with under three cells each distinct cell once) become one candidate
 // sequence: cell by cell (x fastest), atoms in slot order.  The wavefront
-// holds 64 x kCandPasses candidates in registers, shifted by the periodic
+// holds up to 64 x kCandPasses candidates in registers, shifted by the periodic
 // image of their cell, and tests every atom of its own cell against them;
-// the in-range lanes of each test are packed with a ballot, so list entries
-// come out in candidate order.  Full list: every j != i with r < r_c + skin;
+// the in-range lanes of each test are packed with ballots, so list entries
+// come out in candidate order, inner ones first.  Full list: every j != i with r < r_c + skin;
 // half list: only j with a larger slot index.
 //
-// Entries: slot | code << kIndexBits, 2 bits per axis, and kInnerBit for a
-// pair closer than r_d + skin.  FP64 mode: the periodic image (0 none, 1 +L,
+// Entries: slot | code << kIndexBits, 2 bits per axis; a row's inner entries
+// (pairs closer than r_d + skin) come first.  FP64 mode: the periodic image (0 none, 1 +L,
 // 2 -L); compact mixed mode: the unwrapped link-cell offset plus one.  Axes with one or two periodic cells have no
 // unique image per cell; there the image is the minimum one of each pair.
 // Layout: groups of four entries per slot (nbr_at).  Overflow keeps counting, so the
@@ -346,9 +357,26 @@ __global__ void k_cell_table(Buffers b, int32_t n_cells)
     if (k == 13) b.cell_coord[cell] = c[0] | (c[1] << 10) | (c[2] << 20);
 }
 
-constexpr int kCandPasses = 4;
+constexpr int kCandPasses = 4;  // sets of 64 candidates held in registers at most
 
 __device__ __forceinline__ double select_shift(int s, double L) { return s == 1 ? L : (s == 2 ? -L : 0.0); }
+
+// Moves a candidate by the periodic image of its cell.
+template <bool TRI>
+__device__ __forceinline__ void candidate_shift(const Box& bx, int w, double3& x)
+{
+    if (TRI) {
+        double d[3] = {0.0, 0.0, 0.0};
+        apply_shift(bx, w, d[0], d[1], d[2]);
+        x.x += d[0];
+        x.y += d[1];
+        x.z += d[2];
+    } else {
+        x.x += select_shift(w & 3, bx.L[0]);
+        x.y += select_shift((w >> 2) & 3, bx.L[1]);
+        x.z += select_shift((w >> 4) & 3, bx.L[2]);
+    }
+}
 
 
 // Minimum image of one pair along the axes in `amb` (periodic axes with fewer
@@ -385,64 +413,195 @@ struct ListOut {
     int32_t* nbr;
     uint8_t* types;
     int64_t n_slots;
-    int with_types;
 };
 
 
-// Tests atoms s0 .. s0 + n - 1 (lane l holds atom s0 + l in xl) against the
-// candidates in registers and appends the in-range ones to their rows.
-template <int P, bool AMB, bool WIDE, bool SPLIT>
-__device__ __forceinline__ void test_candidates(const ListOut& L, int32_t cap, double rlist2, double rdl2,
-                                                int half_list, int compact, const Box& bx, int amb, int s0, int n,
-                                                const double3& xl,
-                                                const double (&cx)[P], const double (&cy)[P], const double (&cz)[P],
-                                                const int (&ce)[P], const int (&cj)[P], const int (&ct)[P],
-                                                const bool (&live)[P], int& my_count)
+// What a wavefront of the list build works on: one chunk of own atoms and the
+// candidates it tests them against.
+struct ListWork {
+    const double4* pos;
+    const uint8_t* type;    // of the candidates' slots
+    const int2* tab;        // candidate -> {slot, image and offset codes}
+    const uint16_t* kept;   // the candidates that remain, as table indices (pruned)
+    int n_cand;             // candidates to test
+    int s0, n;              // own atoms s0 .. s0 + n - 1; lane l holds atom s0 + l in xl
+    double3 xl;
+    int32_t cap;
+    double rlist2, rdl2;
+    int half_list, compact, amb;
+    bool tabled, pruned, any_wrap;
+    int excl, nb_start, nb_wrap, nb_code;  // lane k: adjacent cell k (without the table)
+};
+
+// Tests the own atoms against NP sets of 64 candidates from candidate g0 on, held
+// in registers, and appends the in-range ones to the atoms' rows.
+//
+// SPLIT: a row holds its inner entries (closer than r_d + skin) first, then the
+// others, each in candidate order.  All sets are tested before an entry is
+// stored, so with every candidate in registers (ONCE) the place behind the inner
+// entries is known in time; otherwise a COUNT sweep over all candidates comes
+// first and `my_outer` enters as that place.  On return lane l's `my_inner` is
+// the number of inner entries of its atom so far and `my_outer` the place behind
+// its last entry.
+template <int NP, bool TRI, bool AMB, bool WIDE, bool SPLIT, bool WT, bool COUNT, bool ONCE>
+__device__ __forceinline__ void test_candidates(const ListOut& L, const ListWork& W, const Box& bx, int g0,
+                                                int& my_inner, int& my_outer)
 {
     const int lane = threadIdx.x & (kWave - 1);
+    double cx[NP], cy[NP], cz[NP];
+    int ce[NP], cj[NP], ct[NP];
+    bool live[NP];
+#pragma unroll
+    for (int u = 0; u < NP; ++u) {
+        const int m0 = g0 + u * kWave + lane;
+        int m = min(m0, W.n_cand - 1);
+        int j, w, code;
+        if (ONCE || W.tabled) {
+            if (W.pruned) m = W.kept[m];
+            const int2 tv = W.tab[m];
+            j = tv.x;
+            w = tv.y & 63;
+            code = (tv.y >> 8) & 63;
+        } else {
+            // the adjacent cell holding candidate m: the last k with excl_k <= m
+            int k = 0;
+#pragma unroll
+            for (int step = kWave / 2; step > 0; step >>= 1)
+                if (__shfl(W.excl, k + step, kWave) <= m) k += step;
+            j = __shfl(W.nb_start, k, kWave) + (m - __shfl(W.excl, k, kWave));
+            w = __shfl(W.nb_wrap, k, kWave);
+            code = __shfl(W.nb_code, k, kWave);
+        }
+        double3 xj = load_xyz(W.pos, j);
+        if (W.any_wrap) candidate_shift<TRI>(bx, w, xj);
+        cx[u] = xj.x;
+        cy[u] = xj.y;
+        cz[u] = xj.z;
+        ce[u] = j | (code << kIndexBits);
+        cj[u] = j;
+        ct[u] = WT ? W.type[j] : 0;
+        live[u] = m0 < W.n_cand;
+    }
     // j != i (full list) or j > i (half list) as one unsigned compare of j - i - 1
-    const uint32_t lim = half_list ? 0x7FFFFFFFu : 0xFFFFFFFFu;
-    for (int ii = 0; ii < n; ++ii) {
-        const int i = s0 + ii;
-        const double xi = bcast_lane(xl.x, ii), yi = bcast_lane(xl.y, ii), zi = bcast_lane(xl.z, ii);
-        int base = __builtin_amdgcn_readlane(my_count, ii);
+    const uint32_t lim = W.half_list ? 0x7FFFFFFFu : 0xFFFFFFFFu;
+    for (int ii = 0; ii < W.n; ++ii) {
+        const int i = W.s0 + ii;
+        const double xi = bcast_lane(W.xl.x, ii), yi = bcast_lane(W.xl.y, ii), zi = bcast_lane(W.xl.z, ii);
+        bool take[NP], in[NP];
+        int e[NP], n_inner = 0;
+#pragma unroll
+        for (int u = 0; u < NP; ++u) {
+            double dx = cx[u] - xi, dy = cy[u] - yi, dz = cz[u] - zi;
+            e[u] = ce[u];
+            if (AMB) min_image_pair(bx, W.amb, W.compact, dx, dy, dz, e[u]);
+            const double r2 = dx * dx + dy * dy + dz * dz;
+            take[u] = live[u] & ((uint32_t)(cj[u] - (i + 1)) < lim) & (r2 < W.rlist2);
+            in[u] = SPLIT && (take[u] & (r2 < W.rdl2));
+            if (SPLIT) n_inner += __popcll(__builtin_amdgcn_ballot_w64(in[u]));
+        }
+        if (COUNT) {
+            if (lane == ii) my_inner += n_inner;
+            continue;
+        }
+        int base_in = ONCE ? 0 : __builtin_amdgcn_readlane(my_inner, ii);
+        int base_out = ONCE ? n_inner : __builtin_amdgcn_readlane(my_outer, ii);
         const uint32_t row = (uint32_t)i * 16u;  // entry k of atom i: row + (k / 4) group_bytes + 4 (k % 4)
 #pragma unroll
-        for (int u = 0; u < P; ++u) {
-            double dx = cx[u] - xi, dy = cy[u] - yi, dz = cz[u] - zi;
-            int e = ce[u];
-            if (AMB) min_image_pair(bx, amb, compact, dx, dy, dz, e);
-            const double r2 = dx * dx + dy * dy + dz * dz;
-            const bool take = live[u] & ((uint32_t)(cj[u] - (i + 1)) < lim) & (r2 < rlist2);
-            if (SPLIT && r2 < rdl2) e |= kInnerBit;  // (otherwise every candidate carries it)
-            const uint64_t mask = __builtin_amdgcn_ballot_w64(take);
-            if (mask == 0) continue;
-            const int rank = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
-                                                            __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
-            // entry base + rank of atom i (the layout of nbr_at)
-            const uint32_t k = (uint32_t)(base + rank);
-            if (take && base + rank < cap) {
+        for (int u = 0; u < NP; ++u) {
+            const uint64_t inner = SPLIT ? __builtin_amdgcn_ballot_w64(in[u]) : 0;
+            const uint64_t outer = __builtin_amdgcn_ballot_w64(take[u]) & ~inner;
+            // the lane's place among its kind
+            const int k_out = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(outer >> 32),
+                                                             __builtin_amdgcn_mbcnt_lo((uint32_t)outer, base_out));
+            int at_row = k_out;
+            if (SPLIT) {
+                const int k_in = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(inner >> 32),
+                                                                __builtin_amdgcn_mbcnt_lo((uint32_t)inner, base_in));
+                at_row = in[u] ? k_in : k_out;
+            }
+            if (take[u] & (at_row < W.cap)) {
+                const uint32_t k = (uint32_t)at_row;  // entry k of atom i (the layout of nbr_at)
                 if (WIDE) {
-                    const int64_t at = nbr_at(base + rank, i, L.n_slots);
-                    L.nbr[at] = e;
-                    if (L.with_types) L.types[at] = (uint8_t)ct[u];
+                    const int64_t at = nbr_at(at_row, i, L.n_slots);
+                    L.nbr[at] = e[u];
+                    if (WT) L.types[at] = (uint8_t)ct[u];
                 } else {
                     const uint32_t off = (k >> 2) * L.group_bytes + ((k & 3u) << 2);
-                    __builtin_amdgcn_raw_buffer_store_b32(e, L.rs, off, row, 0);
-                    if (L.with_types)  // byte offsets a quarter of the entry's
+                    __builtin_amdgcn_raw_buffer_store_b32(e[u], L.rs, off, row, 0);
+                    if (WT)  // byte offsets a quarter of the entry's
                         __builtin_amdgcn_raw_buffer_store_b8((unsigned char)ct[u], L.ts, off >> 2, row >> 2, 0);
                 }
             }
-            base += __popcll(mask);
+            base_in += __popcll(inner);
+            base_out += __popcll(outer);
         }
-        if (lane == ii) my_count = base;
+        if (lane == ii) {
+            my_inner = base_in;
+            my_outer = base_out;
+        }
     }
+}
+
+// Smallest values of the wavefront's lanes 0 .. n - 1 (the lanes beyond repeat
+// one of those): within rows of 16 lanes by shifts, then, for n > 16, across the
+// rows; a lane without a source keeps its value.  Written as one block of DPP
+// minima, one instruction per step and value (the builtins take four: a move,
+// two quieting maxima, the minimum); a value is read five instructions after it
+// was written, beyond the two wait states DPP asks for.
+__device__ __forceinline__ void wave_min(float (&v)[6], int n)
+{
+#define MDK_DPP_STEP(ctrl)                      \
+    "v_min_f32_dpp %0, %0, %0 " ctrl "\n\t"     \
+    "v_min_f32_dpp %1, %1, %1 " ctrl "\n\t"     \
+    "v_min_f32_dpp %2, %2, %2 " ctrl "\n\t"     \
+    "v_min_f32_dpp %3, %3, %3 " ctrl "\n\t"     \
+    "v_min_f32_dpp %4, %4, %4 " ctrl "\n\t"     \
+    "v_min_f32_dpp %5, %5, %5 " ctrl "\n\t"
+    asm volatile("s_nop 1\n\t"  // values just written
+                 MDK_DPP_STEP("row_shr:1 row_mask:0xf bank_mask:0xf")
+                 MDK_DPP_STEP("row_shr:2 row_mask:0xf bank_mask:0xf")
+                 MDK_DPP_STEP("row_shr:4 row_mask:0xf bank_mask:0xf")
+                 MDK_DPP_STEP("row_shr:8 row_mask:0xf bank_mask:0xf")
+                 : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]));
+    int last = 15;  // lane 15 of a row holds its minimum
+    if (n > 16) {
+        asm volatile("s_nop 1\n\t"
+                     MDK_DPP_STEP("row_bcast:15 row_mask:0xa bank_mask:0xf")
+                     MDK_DPP_STEP("row_bcast:31 row_mask:0xc bank_mask:0xf")
+                     : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]));
+        last = kWave - 1;
+    }
+#undef MDK_DPP_STEP
+#pragma unroll
+    for (int k = 0; k < 6; ++k) v[k] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v[k]), last));
+}
+
+// Inclusive sums over the first 32 lanes (lanes 27 .. 31 hold zeros here).
+__device__ __forceinline__ int scan32(int v)
+{
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);  // row_shr:1, 2, 4, 8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);  // row_bcast:15 into the next row
+    return v;
+}
+
+// Largest list length over the wavefront, one atomic per wavefront.
+__device__ __forceinline__ void wave_max_flag(int v, int32_t* flag)
+{
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1) v = max(v, __shfl_xor(v, off, kWave));
+    // The flag only grows, so a plain (possibly stale) read filters out the
+    // atomics that cannot raise it: a kernel with many wavefronts would
+    // otherwise serialise on one address.
+    if ((threadIdx.x & (kWave - 1)) == 0 && v > 0 && v > *flag) atomicMax(flag, v);
 }
 
 // TRI: sheared cells (candidate shifts are edge-vector sums), a separate
 // instantiation so the orthorhombic build keeps its short candidate loop.
-// SPLIT: mark the inner entries (r < r_d + skin); otherwise every entry is
-// inner (one precision's density pass gains nothing from the mark).
+// SPLIT: the inner entries (r < r_d + skin) of a row come first; otherwise every
+// entry is inner.
 // WT: several species (each entry's type byte is stored beside it).
 // gate: the automatic rebuild's replica flags (NULL: every replica).
 // copy_back: also copy each own atom's sorted state from (p, q) into
@@ -459,10 +618,9 @@ __device__ __forceinline__ void list_cell(const Buffers& b, int p, int q, int64_
     const int n_own = uniform(b.cell_count[cell]);
     if (n_own == 0) return;
     const int s_own = uniform(b.cell_start[cell]);
+    const int seen = b.flags[F_MAX_COUNT];  // (read early, or its latency would end every wavefront)
     const DevReplica& R = b.reps[r];
     const Box bx = load_box(R);
-    const int cpk = uniform(b.cell_coord[cell]);
-    int c[3] = {cpk & 1023, (cpk >> 10) & 1023, cpk >> 20};
     int amb = 0;  // periodic axes with fewer than three cells
 #pragma unroll
     for (int a = 0; a < 3; ++a)
@@ -479,18 +637,13 @@ __device__ __forceinline__ void list_cell(const Buffers& b, int p, int q, int64_
             nb_count = b.cell_count[adj.x];
         }
     }
-    // sheared cells: whether any adjacent cell lies across a face (interior
-    // cells, most of a large cell, skip the edge-vector shifts)
-    const bool any_wrap = TRI && __ballot(nb_wrap != 0) != 0;
+    // whether any adjacent cell lies across a face (interior cells, most of a
+    // large box, skip the candidates' shifts)
+    const bool any_wrap = __ballot(nb_wrap != 0) != 0;
     // exclusive prefix of the candidate counts over the 27 lanes
-    int incl = nb_count;
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-        const int v = __shfl_up(incl, off, kWave);
-        if (lane >= off) incl += v;
-    }
-    const int excl = incl - nb_count;
-    const int total = uniform(__shfl(incl, kWave - 1, kWave));
+    const int incl = scan32(nb_count);
+    const int excl = lane < 27 ? incl - nb_count : INT32_MAX;  // (lanes beyond never start at a candidate)
+    const int total = __builtin_amdgcn_readlane(incl, 26);
 
     // candidate table of this wave: slot and codes of candidate m, written by
     // the 27 lanes of the adjacent cells (lane k its own cell's run), read back
@@ -507,6 +660,12 @@ __device__ __forceinline__ void list_cell(const Buffers& b, int p, int q, int64_
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
 
+    // the candidates that remain for a chunk of own atoms, as table indices
+    __shared__ uint16_t kept_table[kBlock / kWave][kCandTable];
+    uint16_t* kept = kept_table[threadIdx.x / kWave];
+    const float prune = sqrtf((float)rlist2) + 1e-3f;
+    const float prune2 = prune * prune;
+
     const double4* __restrict__ pos = b.pos[p];
     // (WIDE: the buffer resources are unused; their sizes wrap harmlessly)
     ListOut L;
@@ -517,72 +676,91 @@ __device__ __forceinline__ void list_cell(const Buffers& b, int p, int q, int64_
     L.nbr = b.nbr;
     L.types = b.ntype;
     L.n_slots = n_slots;
-    L.with_types = WT;
     for (int i0 = 0; i0 < n_own; i0 += kWave) {
         const int n_chunk = min(kWave, n_own - i0);
         // lane l holds atom s_own + i0 + l; the test loop broadcasts it
         const double3 xl = load_xyz(pos, s_own + i0 + min(lane, n_chunk - 1));
-        int my_count = 0;  // lane l: entries of that atom so far
-        for (int g0 = 0; g0 < total; g0 += kWave * kCandPasses) {
-            double cx[kCandPasses], cy[kCandPasses], cz[kCandPasses];
-            int ce[kCandPasses], cj[kCandPasses], ct[kCandPasses];
-            bool live[kCandPasses];
+        ListWork W = {pos, b.type[q], tab, kept, total, s_own + i0, n_chunk, xl, cap, rlist2, rdl2, half_list, compact, amb,
+                      tabled, false, any_wrap, excl, nb_start, nb_wrap, nb_code};
+        // Candidates beyond the list radius of the box around these atoms are
+        // left out first (in FP32 relative to the first own atom, with a margin
+        // of 0.001 A: rounding below 1000 A is 6e-5 A; not where pairs take their
+        // minimum image one by one).  The tests, ~20 vector instructions per own
+        // atom and 64 candidates, bound this kernel, and about half of the 27
+        // cells' candidates go.  It pays from ~10 atoms per cell: Fe-C replicas
+        // at a 0.8 A skin 211 -> 157 us per build with the gather, the fcc slab
+        // 120 -> 95, sheared 128,000 atoms 81 -> 60; at 7 atoms per cell the
+        // leaving out costs what it saves (1,013,760 atoms FP64 291 -> 305).
+        if (tabled && amb == 0) {
+            const double xr = bcast_lane(xl.x, 0), yr = bcast_lane(xl.y, 0), zr = bcast_lane(xl.z, 0);
+            const float ox = (float)(xl.x - xr), oy = (float)(xl.y - yr), oz = (float)(xl.z - zr);
+            float lo[6] = {ox, oy, oz, -ox, -oy, -oz};
+            wave_min(lo, n_chunk);
+            const float hx = -lo[3], hy = -lo[4], hz = -lo[5];
+            if (hx - lo[0] < 1000.0f && hy - lo[1] < 1000.0f && hz - lo[2] < 1000.0f) {
+                int n_cand = 0;
+                for (int g0 = 0; g0 < total; g0 += 2 * kWave) {
+                    float px[2], py[2], pz[2];
 #pragma unroll
-            for (int u = 0; u < kCandPasses; ++u) {
-                const int m0 = g0 + u * kWave + lane;
-                const int m = min(m0, total - 1);
-                int j, w, code;
-                if (tabled) {
-                    const int2 tv = tab[m];
-                    j = tv.x;
-                    w = tv.y & 63;
-                    code = (tv.y >> 8) & 63;
-                } else {
-                    // the adjacent cell holding candidate m: the last k with excl_k <= m
-                    int k = 0;
+                    for (int u = 0; u < 2; ++u) {  // both loads before the first test
+                        const int m0 = g0 + u * kWave;
+                        if (m0 >= total) continue;
+                        const int2 tv = tab[min(m0 + lane, total - 1)];
+                        double3 xj = load_xyz(pos, tv.x);
+                        if (any_wrap) candidate_shift<TRI>(bx, tv.y & 63, xj);
+                        px[u] = (float)(xj.x - xr);
+                        py[u] = (float)(xj.y - yr);
+                        pz[u] = (float)(xj.z - zr);
+                    }
 #pragma unroll
-                    for (int step = kWave / 2; step > 0; step >>= 1)
-                        if (__shfl(excl, k + step, kWave) <= m) k += step;
-                    j = __shfl(nb_start, k, kWave) + (m - __shfl(excl, k, kWave));
-                    w = __shfl(nb_wrap, k, kWave);
-                    code = __shfl(nb_code, k, kWave);
+                    for (int u = 0; u < 2; ++u) {
+                        const int m0 = g0 + u * kWave;
+                        if (m0 >= total) continue;
+                        const float ex = fmaxf(fmaxf(lo[0] - px[u], px[u] - hx), 0.0f),
+                                    ey = fmaxf(fmaxf(lo[1] - py[u], py[u] - hy), 0.0f),
+                                    ez = fmaxf(fmaxf(lo[2] - pz[u], pz[u] - hz), 0.0f);
+                        const bool keep = m0 + lane < total && fmaf(ex, ex, fmaf(ey, ey, ez * ez)) <= prune2;
+                        const uint64_t mask = __builtin_amdgcn_ballot_w64(keep);
+                        const int at = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                                                      __builtin_amdgcn_mbcnt_lo((uint32_t)mask, n_cand));
+                        if (keep) kept[at] = (uint16_t)(m0 + lane);
+                        n_cand += __popcll(mask);
+                    }
                 }
-                const double3 xj = load_xyz(pos, j);
-                if (TRI) {  // the image cell's edge-vector shift
-                    double dsh[3] = {0.0, 0.0, 0.0};
-                    if (any_wrap) apply_shift(bx, w & 63, dsh[0], dsh[1], dsh[2]);
-                    cx[u] = xj.x + dsh[0];
-                    cy[u] = xj.y + dsh[1];
-                    cz[u] = xj.z + dsh[2];
-                } else {
-                    cx[u] = xj.x + select_shift(w & 3, bx.L[0]);
-                    cy[u] = xj.y + select_shift((w >> 2) & 3, bx.L[1]);
-                    cz[u] = xj.z + select_shift((w >> 4) & 3, bx.L[2]);
-                }
-                ce[u] = j | (code << kIndexBits) | (SPLIT ? 0 : kInnerBit);
-                cj[u] = j;
-                ct[u] = WT ? b.type[q][j] : 0;
-                live[u] = m0 < total;
+                W.n_cand = n_cand;
+                W.pruned = true;
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
             }
-            if (amb)
-                test_candidates<kCandPasses, true, WIDE, SPLIT>(L, cap, rlist2, rdl2, half_list, compact, bx, amb,
-                                                                s_own + i0, n_chunk, xl, cx, cy, cz, ce, cj, ct, live,
-                                                                my_count);
-            else
-                test_candidates<kCandPasses, false, WIDE, SPLIT>(L, cap, rlist2, rdl2, half_list, compact, bx, amb,
-                                                                 s_own + i0, n_chunk, xl, cx, cy, cz, ce, cj, ct, live,
-                                                                 my_count);
         }
-        // per-atom epilogue: count, overflow flag, compact record
+        // lane l: inner entries of that atom so far, and the place behind its others
+        int my_inner = 0, my_outer = 0;
+        if (W.pruned && W.n_cand <= kWave * kCandPasses) {
+            if (W.n_cand <= kWave) test_candidates<1, TRI, false, WIDE, SPLIT, WT, false, true>(L, W, bx, 0, my_inner, my_outer);
+            else if (W.n_cand <= 2 * kWave)
+                test_candidates<2, TRI, false, WIDE, SPLIT, WT, false, true>(L, W, bx, 0, my_inner, my_outer);
+            else if (W.n_cand <= 3 * kWave)
+                test_candidates<3, TRI, false, WIDE, SPLIT, WT, false, true>(L, W, bx, 0, my_inner, my_outer);
+            else test_candidates<4, TRI, false, WIDE, SPLIT, WT, false, true>(L, W, bx, 0, my_inner, my_outer);
+        } else {
+            if (SPLIT) {  // count the inner entries; the others go behind them
+                for (int g0 = 0; g0 < W.n_cand; g0 += 2 * kWave)
+                    if (amb) test_candidates<2, TRI, true, WIDE, SPLIT, WT, true, false>(L, W, bx, g0, my_inner, my_outer);
+                    else test_candidates<2, TRI, false, WIDE, SPLIT, WT, true, false>(L, W, bx, g0, my_inner, my_outer);
+                my_outer = my_inner;
+                my_inner = 0;
+            }
+            for (int g0 = 0; g0 < W.n_cand; g0 += 2 * kWave)
+                if (amb) test_candidates<2, TRI, true, WIDE, SPLIT, WT, false, false>(L, W, bx, g0, my_inner, my_outer);
+                else test_candidates<2, TRI, false, WIDE, SPLIT, WT, false, false>(L, W, bx, g0, my_inner, my_outer);
+        }
+        const int my_count = my_outer;
+        // per-atom epilogue: counts, overflow flag
         const int i = s_own + i0 + lane;
         if (lane < n_chunk) {
             b.ncount[i] = min(my_count, cap);
-            b.cellxyz[i] = make_int4(c[0], c[1], c[2], 0);
-            if (compact) {
-                int4 rq;
-                if (!compact_coords<TRI ? 2 : 1>(R, c, xl.x, xl.y, xl.z, rq)) atomicAdd(&b.flags[F_COMPACT], 1);
-                b.rec[0][i] = rq;
-            }
+            b.ninner[i] = min(SPLIT ? my_inner : my_count, cap);
             if (copy_back) {  // (no lane of this kernel reads the buffers written here)
                 const int pn = p ^ 1, qn = q ^ 1;
                 b.pos[pn][i] = pos[i];
@@ -603,7 +781,8 @@ __device__ __forceinline__ void list_cell(const Buffers& b, int p, int q, int64_
                 }
             }
         }
-        wave_max_flag(lane < n_chunk ? my_count : 0, &b.flags[F_MAX_COUNT]);
+        if (__builtin_amdgcn_ballot_w64(lane < n_chunk && my_count > seen) != 0)
+            wave_max_flag(lane < n_chunk ? my_count : 0, &b.flags[F_MAX_COUNT]);
     }
 }
 
@@ -612,7 +791,7 @@ __device__ __forceinline__ void list_cell(const Buffers& b, int p, int q, int64_
 // complete in order, so its candidate table is simply refilled for the next
 // cell); a separate instantiation, since the loop keeps more registers live.
 template <bool TRI, bool WIDE, bool SPLIT, bool WT, bool LOOP>
-__global__ __launch_bounds__(kBlock) void k_cell_list(Buffers b, int p, int q, int64_t n_slots, int32_t n_cells,
+__global__ __launch_bounds__(kBlock, TRI ? 4 : LOOP ? 5 : 6) void k_cell_list(Buffers b, int p, int q, int64_t n_slots, int32_t n_cells,
                                                       int32_t cap, double rlist2, double rdl2, int half_list,
                                                       int compact, const int32_t* __restrict__ gate, int copy_back)
 {
@@ -646,7 +825,7 @@ void launch_rebuild(const Buffers& b, int p, int q, const KernelShape& k, double
     hipLaunchKernelGGL(k_scan_add, dim3(nb), dim3(kScanBlock), 0, s, b, k.n_cells, gate);
     hipLaunchKernelGGL(k_scatter, dim3(slot_blocks), dim3(kBlock), 0, s, b, k.n_slots, gate);
     hipLaunchKernelGGL(k_sort_cells, dim3(slot_blocks), dim3(kBlock), 0, s, b, q, k.n_slots, gate);
-    hipLaunchKernelGGL(k_gather, dim3(slot_blocks), dim3(kBlock), 0, s, b, p, q, k.n_slots, gate);
+    hipLaunchKernelGGL(k_gather, dim3(slot_blocks), dim3(kBlock), 0, s, b, p, q, k.n_slots, k.compact, gate);
 }
 
 // Displacement check of the automatic rebuild: the same criterion as the skin
@@ -683,9 +862,9 @@ void launch_build_list(const Buffers& b, int p, int q, const KernelShape& k, dou
                        int half_list, const int32_t* gate, int copy_back, hipStream_t s)
 {
     int64_t blocks = ((int64_t)k.n_cells + kBlock / kWave - 1) / (kBlock / kWave);
-    if (gate) blocks = std::min<int64_t>(blocks, kGatedBlocks / 2);
+    if (gate) blocks = std::min<int64_t>(blocks, kGatedBlocks * 5 / 8);
     const bool wide = (uint64_t)k.n_slots * 16 * (uint64_t)((k.cap + 2 * kChunk - 1) / kChunk) >= ((uint64_t)1 << 32);
-    const bool split = k.split_list && !half_list && rdl2 < rlist2;
+    const bool split = !half_list && rdl2 < rlist2;
     const int which = (k.tri ? 8 : 0) | (wide ? 4 : 0) | (split ? 2 : 0) | (k.list_types ? 1 : 0);
     using Kern = void (*)(Buffers, int, int, int64_t, int32_t, int32_t, double, double, int, int, const int32_t*, int);
     // [gated][TRI WIDE SPLIT WT]

@@ -318,17 +318,6 @@ __device__ __forceinline__ void embed(double c, double rho, double& F, double& d
     }
 }
 
-// Largest list length over the wavefront, one atomic per wavefront.
-__device__ __forceinline__ void wave_max_flag(int v, int32_t* flag)
-{
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) v = max(v, __shfl_xor(v, off, kWave));
-    // The flag only grows, so a plain (possibly stale) read filters out the
-    // atomics that cannot raise it: a kernel with many wavefronts would
-    // otherwise serialise on one address.
-    if ((threadIdx.x & (kWave - 1)) == 0 && v > 0 && v > *flag) atomicMax(flag, v);
-}
-
 // ---------------------------------------------------------------------------
 // Pair-function evaluation.  EV_TABLE: every cubic-knot sum is re-expanded
 // exactly as a cubic in the local coordinate u = r - b w of a bin b of width w

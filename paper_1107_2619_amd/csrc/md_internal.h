@@ -37,14 +37,13 @@ constexpr int kHaloTableBytes = 5120;  // LDS of a brick's halo table (bound che
 constexpr int kBrickMaxDim = 4;
 
 // Neighbour-list entry: slot index in the low kIndexBits bits, the periodic
-// image shift (2 bits per axis) in the six above, and in the global list the
-// sign bit set for an inner entry: a pair closer than r_d + skin at the build,
-// r_d the largest density knot.  The others stay beyond every density cutoff
-// until the next build, so the density pass gathers only inner entries.
+// image shift (2 bits per axis) in the six above.  In the global full list the
+// inner entries of a row (pairs closer than r_d + skin at the build, r_d the
+// largest density knot) come first.  The others stay beyond every density cutoff
+// until the next build, so the density pass reads only the inner entries.
 constexpr int kIndexBits = 25;
 constexpr int kIndexMask = (1 << kIndexBits) - 1;
 constexpr int kCodeMask = 63;
-constexpr int32_t kInnerBit = INT32_MIN;
 constexpr int kChunk = 4;  // neighbours whose loads are issued together (one 16-byte list load)
 
 // Neighbour-list layout (global kernels): entry k of slot t at
@@ -185,6 +184,7 @@ struct Buffers {
     int32_t* stage_src;   // [n_bricks][halo_cap] slot | shift code of each staging position
     uint16_t* own_li;     // [Np] staging position of each atom within its own brick
     int32_t* ncount;      // [Np]
+    int32_t* ninner;      // [Np] inner entries of the slot's row (global full list)
     int32_t* cell_of;     // [Np]
     int32_t* perm;        // [Np] new slot -> old slot
     int32_t* cell_start;  // [C]
@@ -253,8 +253,6 @@ struct KernelShape {
     int32_t pairs;     // LDS bricks with each pair of two own atoms once (MD_OPT_KERNEL = 2)
     int32_t nchunk;    // neighbour records in flight per thread in the global kernels: 2, 4 or 8
     int32_t list_types; // the global list also stores its entries' type bytes (several species)
-    int32_t split_list; // the global list marks its inner entries (FP64: the density pass then
-                        // gathers only those)
     int32_t split;     // 1 = the global kernels deal each atom's neighbours to kSplit waves
     int32_t chunked;  // 1 = per-replica sums of the thermostat and barostat start with
                       // per-chunk sums (some replica spans more than kChunkedSumWaves waves)
@@ -271,7 +269,7 @@ void launch_load_state(const Buffers& b, int p, int q, const md_state& st, const
 // others).
 void launch_rebuild(const Buffers& b, int p, int q, const KernelShape& k, double half_skin2,
                     int half_list, const int32_t* gate, hipStream_t s);
-// rdl2 = (r_d + skin)^2 marks the inner entries (rlist2: every entry).
+// rdl2 = (r_d + skin)^2 bounds the inner entries (rlist2: every entry).
 // copy_back: the list is built from the sorted state in (p, q) and each own
 // atom's state is copied into (p ^ 1, q ^ 1) (automatic rebuilds, which keep
 // the ping-pong indices).

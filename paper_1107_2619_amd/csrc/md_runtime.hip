@@ -207,9 +207,6 @@ KernelShape shape(const md_ctx* c)
     // few atoms: up to two one-thread wavefronts per SIMD (see kernels_global.h)
     k.split = c->Np <= (int64_t)2 * kSimds * kWave;
     k.list_types = c->single ? 0 : 1;
-    // FP64 density passes gather 24 bytes per neighbour and gain from skipping
-    // the outer entries; the 16-byte compact records of mixed precision do not
-    k.split_list = c->precision == MD_FP64 ? 1 : 0;
     return k;
 }
 
@@ -554,6 +551,7 @@ void plan_workspace(md_ctx* c)
         Np / kWave * kEnergyTerms * 8,                       // wave_terms
         C * 4,                                               // bin_count (C_alloc)
         2 * ((size_t)c->R + 1) * 4,                          // gate
+        Np * 4,                                              // ninner
     };
     c->off.clear();
     size_t o = 0;
@@ -646,6 +644,7 @@ void bind_buffers(md_ctx* c)
     at(b.wave_terms);
     at(b.bin_count);
     at(b.gate);
+    at(b.ninner);
 }
 
 hipStream_t as_stream(void* s) { return reinterpret_cast<hipStream_t>(s); }
