@@ -82,11 +82,9 @@ __device__ __forceinline__ int4 record_load(__amdgpu_buffer_rsrc_t rs, int j)
 //   - k_density_split, k_force_split: the groups of 64 atoms are dealt to the
 //     waves of a workgroup.
 //
-// The cost of the one-thread form is set by the number of vector-memory
-// accesses per neighbour (the L1 resolves about one lane's access per clock
-// per CU), not by bytes or arithmetic: FP64 mode gathers a 32-byte
-// {x, y, z, F'} record (two accesses), the compact mixed mode a 16-byte record
-// (one access).
+// FP64 mode reads a 32-byte {x, y, z, F'} record per neighbour, from LDS where it
+// is one of the workgroup's own slots (Stage), the compact mixed mode a 16-byte
+// record from the caches.
 //
 // NCH: neighbour records in flight per thread (2, 4 or 8; the autotuner picks
 // it): more hide more gather latency, fewer free registers for more waves.
@@ -94,9 +92,126 @@ __device__ __forceinline__ int4 record_load(__amdgpu_buffer_rsrc_t rs, int j)
 // TL: several species with all their tables staged in LDS, in workgroups of
 // kTableBlock threads that share one copy (one species always stages its own).
 
+// The FP64 records of a workgroup's own slots, staged in LDS, where 63% of a
+// crystal's neighbours lie (256 slots; 70% of 512): the L1 resolves one lane's
+// 16-byte access per clock and CU, and an FP64 record takes two, which bound the
+// force pass (74% of its time); from LDS a record costs a quarter of that.  Step
+// times, from the caches against staged: 218,972 atoms 59.8 and 60.7 us, 278,404
+// atoms 71.4 -> 67.3, 427,680 atoms 96.3 -> 88.2, 1,013,760 atoms 183.6 -> 162.6
+// (force 98 -> 86, density 61 -> 52).  Below four wavefronts per SIMD latency
+// binds and staging adds to it (KernelShape::stage).  The 16-byte compact records
+// of mixed precision gain nothing (1,013,760 atoms 163 us either way): there the
+// vector units are as busy as the L1; nor do several species, whose workgroups of
+// 1024 hold all tables (1,024,000 atoms 258 us either way).  Workgroups of 512 do
+// as well at 1,013,760 atoms (165.5 us) and worse at 427,680 (99, the last round
+// of workgroups).
+//
+// The two halves of a record lie in separate arrays, so that a random 16-byte read
+// may fall on any bank.  FULL: with F' (the force pass).
+//
+// The staged records are read through LDS pointers (address space 3): through
+// plain ones the compiler may merge a lane's LDS and global read into one flat
+// load, which costs the whole gain.
+typedef double double2v __attribute__((ext_vector_type(2)));
+
+template <bool FULL>
+struct Stage {
+    __attribute__((address_space(3))) unsigned char* mem;
+    int t0;
+    static constexpr size_t kBytes = kBlock * (FULL ? 32 : 24);
+    __device__ __forceinline__ Stage(unsigned char* m, int first)
+        : mem((__attribute__((address_space(3))) unsigned char*)m), t0(first)
+    {
+    }
+    __device__ __forceinline__ __attribute__((address_space(3))) double2v* xy() const
+    {
+        return (__attribute__((address_space(3))) double2v*)mem;
+    }
+    __device__ __forceinline__ __attribute__((address_space(3))) double2v* zf() const { return xy() + kBlock; }
+    __device__ __forceinline__ __attribute__((address_space(3))) double* zs() const
+    {
+        return (__attribute__((address_space(3))) double*)(mem + 16 * kBlock);
+    }
+    __device__ __forceinline__ void put(unsigned l, const double3& x) const
+    {
+        xy()[l] = (double2v){x.x, x.y};
+        zs()[l] = x.z;
+    }
+    __device__ __forceinline__ void put(unsigned l, const double4& x) const
+    {
+        xy()[l] = (double2v){x.x, x.y};
+        zf()[l] = (double2v){x.z, x.w};
+    }
+    // the record of staged slot t0 + l
+    __device__ __forceinline__ void get(unsigned l, double3& x) const
+    {
+        const double2v a = xy()[l];
+        x = make_double3(a.x, a.y, zs()[l]);
+    }
+    __device__ __forceinline__ void get(unsigned l, double4& x) const
+    {
+        const double2v a = xy()[l], c = zf()[l];
+        x = make_double4(a.x, a.y, c.x, c.y);
+    }
+    static __device__ __forceinline__ void load(const double4* pos, int j, double3& x) { x = load_xyz(pos, j); }
+    static __device__ __forceinline__ void load(const double4* pos, int j, double4& x) { x = pos[j]; }
+    // The records of entries e: all LDS reads (some record for the lanes whose
+    // neighbour is not staged), then the other lanes' loads.
+    template <bool STAGE, int NCH, typename V>
+    __device__ __forceinline__ void gather(const double4* pos, const int (&e)[NCH], V (&x)[NCH]) const
+    {
+        if constexpr (!STAGE) {
+#pragma unroll
+            for (int u = 0; u < NCH; ++u) load(pos, e[u] & kIndexMask, x[u]);
+        } else {
+#pragma unroll
+            for (int u = 0; u < NCH; ++u) get(min((unsigned)((e[u] & kIndexMask) - t0), (unsigned)kBlock - 1), x[u]);
+#pragma unroll
+            for (int u = 0; u < NCH; ++u)
+                if ((unsigned)((e[u] & kIndexMask) - t0) >= (unsigned)kBlock) load(pos, e[u] & kIndexMask, x[u]);
+        }
+    }
+};
+
+// FP64 value tables in LDS as two planes of 16-byte halves {c0, c1}, {c2, c3}: at
+// the 32-byte stride of the records a half could fall on half the banks only
+// (density pass with staged records at 1,013,760 atoms: 65.2 -> 52.5 us).
+template <typename R, int EV>
+constexpr bool in_planes() { return EV == EV_TABLE && sizeof(R) == 8; }
+
+template <typename R, int EV>
+__device__ __forceinline__ void value_fill(R* dst, const R* src, int bins)
+{
+    if constexpr (in_planes<R, EV>()) {
+        const double2* from = reinterpret_cast<const double2*>(src);
+        double2* to = reinterpret_cast<double2*>(dst);
+        for (int i = threadIdx.x; i < 2 * bins; i += blockDim.x) to[(i & 1) * bins + (i >> 1)] = from[i];
+    } else {
+        lds_fill(dst, src, bins * value_stride(EV));
+    }
+}
+
+// density_term from the LDS copy of `bins` bins (LDS) or from global memory.
+template <typename R, bool SINGLE, int NDK, int EV, bool LDS>
+__device__ __forceinline__ R density_value(const PotArgs& P, const DevPotential& G, const R* tab, int si, int sj,
+                                           double r)
+{
+    if constexpr (LDS && in_planes<R, EV>()) {
+        const int bin = (int)(r * P.inv_w);
+        const double u = fma(-(double)bin, P.w, r);
+        const int at = (SINGLE ? 0 : si * G.ns + sj) * P.nbt + bin;
+        const double2* t = reinterpret_cast<const double2*>(tab);
+        const double2 lo = t[at], hi = t[(SINGLE ? 1 : P.ns * P.ns) * P.nbt + at];
+        const double c[4] = {lo.x, lo.y, hi.x, hi.y};
+        return cubic(c, u);
+    } else {
+        return density_term<R, SINGLE, NDK, EV>(P, G, tab, si, sj, r);
+    }
+}
+
 // One neighbour's term of the density sum (Eq. Ucoh, the argument of F),
 // accumulated in FP64 in both precision modes.
-template <typename R, bool SINGLE, int NDK, int EV, int CMP>
+template <typename R, bool SINGLE, int NDK, int EV, int CMP, bool LDS>
 __device__ __forceinline__ void density_pair(const PotArgs& P, const DevPotential& G, const R* tab,
                                              const DevReplica& Rp, const Box& bx, int e, int si, int sj,
                                              const double3& xi, const int4& qb, const double3& xj, const int4& qj,
@@ -115,7 +230,7 @@ __device__ __forceinline__ void density_pair(const PotArgs& P, const DevPotentia
     const double r2 = fma(dx, dx, fma(dy, dy, dz * dz));
     if (!(r2 < P.rc2)) return;
     const double r = r2 * inv_dist<R>(r2);
-    sum += (double)density_term<R, SINGLE, NDK, EV>(P, G, tab, si, sj, r);
+    sum += (double)density_value<R, SINGLE, NDK, EV, LDS>(P, G, tab, si, sj, r);
 }
 
 // One neighbour's term of the force (and energy) sums.  tj: the neighbour's
@@ -186,28 +301,32 @@ __device__ __forceinline__ void density_epilogue(const Buffers& b, int p, int64_
 }
 
 // Density pass, one thread per atom.
-template <typename R, bool SINGLE, int NPK, int NDK, int EV, int CMP, int NCH, bool TL>
+template <typename R, bool SINGLE, int NPK, int NDK, int EV, int CMP, int NCH, bool TL, bool STAGE>
 __global__ __launch_bounds__(TL ? kTableBlock : kBlock) void k_density(Buffers b, int p, int q, int64_t n_slots,
                                                                         PotArgs P, int energy)
 {
     extern __shared__ __align__(16) unsigned char smem[];
+    const int64_t t0 = logical_block() * blockDim.x, t = t0 + threadIdx.x;
+    const double4* __restrict__ pos = b.pos[p];
+    const Stage<false> S(smem, (int)t0);
+    double3 xi = make_double3(0.0, 0.0, 0.0);
+    if (!CMP && t < n_slots) {
+        xi = load_xyz(pos, t);
+        if (STAGE) S.put(threadIdx.x, xi);
+    }
     const R* tab = tables<R>(b).dens;
     if (EV != EV_KNOTS && (SINGLE || TL)) {
-        R* s = reinterpret_cast<R*>(smem);
-        lds_fill(s, tab, (SINGLE ? 1 : P.ns * P.ns) * P.nbt * value_stride(EV));
-        __syncthreads();
+        R* s = reinterpret_cast<R*>(smem + (STAGE ? S.kBytes : 0));
+        value_fill<R, EV>(s, tab, (SINGLE ? 1 : P.ns * P.ns) * P.nbt);
         tab = s;
     }
-    const int64_t t = global_thread();
+    if (STAGE || (EV != EV_KNOTS && (SINGLE || TL))) __syncthreads();
     if (t >= n_slots) return;
     const DevReplica& Rp = b.reps[uniform(b.rep_of_wave[t / kWave])];
     if (t - Rp.slot_off >= Rp.n_atoms) return;
     const Box bx = load_box(Rp);
     const DevPotential& G = *b.pot;
-    const double4* __restrict__ pos = b.pos[p];
-    const int4* __restrict__ rec = b.rec[0];
-    const double3 xi = CMP ? make_double3(0.0, 0.0, 0.0) : load_xyz(pos, t);
-    const int4 qi = CMP ? rec[t] : make_int4(0, 0, 0, 0);
+    const int4 qi = CMP ? b.rec[0][t] : make_int4(0, 0, 0, 0);
     const int4 qb = compact_base(qi);
     const __amdgpu_buffer_rsrc_t rs = record_rsrc(b.rec[0], n_slots);
     const int si = b.type[q][t] & 0x3F;
@@ -246,14 +365,14 @@ __global__ __launch_bounds__(TL ? kTableBlock : kBlock) void k_density(Buffers b
             for (int u = 0; u < NCH; ++u) {
                 e[u] = kb + u < n ? v[sb * NCH + u] : (int)t;
                 if (CMP) qs[u] = record_load(rs, e[u] & kIndexMask);
-                else xs[u] = load_xyz(pos, e[u] & kIndexMask);
             }
+            if (!CMP) S.template gather<STAGE, NCH>(pos, e, xs);
 #pragma unroll
             for (int u = 0; u < NCH; ++u) {
                 if (kb + u >= n) break;
                 const int ku = sb * NCH + u;  // entry within the groups loaded
                 const int sj = SINGLE ? 0 : (int)((tv[ku >> 2] >> (8 * (ku & 3))) & 0x3F);
-                density_pair<R, SINGLE, NDK, EV, CMP>(P, G, tab, Rp, bx, e[u], si, sj, xi, qb, xs[u], qs[u],
+                density_pair<R, SINGLE, NDK, EV, CMP, SINGLE || TL>(P, G, tab, Rp, bx, e[u], si, sj, xi, qb, xs[u], qs[u],
                                                       sum[ku >> 2]);
             }
         }
@@ -316,7 +435,7 @@ __global__ __launch_bounds__(kWave * kSplit) void k_density_split(Buffers b, int
     const R* tab = tables<R>(b).dens;
     if (EV != EV_KNOTS && SINGLE) {
         R* s = reinterpret_cast<R*>(smem);
-        lds_fill(s, tab, P.nbt * value_stride(EV));
+        value_fill<R, EV>(s, tab, P.nbt);
         tab = s;
     }
     double rho = 0.0;
@@ -340,7 +459,7 @@ __global__ __launch_bounds__(kWave * kSplit) void k_density_split(Buffers b, int
         for (int u = 0; u < kChunk; ++u) {
             if (kb + u >= n) break;
             const int sj = SINGLE ? 0 : (int)((tv >> (8 * u)) & 0x3F);
-            density_pair<R, SINGLE, NDK, EV, CMP>(P, G, tab, Rp, bx, e[u], si, sj, xi, qb, xs[u], qs[u], sum);
+            density_pair<R, SINGLE, NDK, EV, CMP, SINGLE>(P, G, tab, Rp, bx, e[u], si, sj, xi, qb, xs[u], qs[u], sum);
         }
         const bool more = __ballot(n > (g0 + kSplit) * kChunk) != 0;  // alike in every wave
         if (more && kb + kSplit * kChunk < n) {
@@ -390,26 +509,33 @@ __device__ __forceinline__ void force_epilogue(const Buffers& b, int p, int q, i
 // EN = 4: the energies and virial of energy mode 1, summed per wavefront in the
 // kernel (the reduction then reads one record per 64 atoms).
 template <typename R, bool SINGLE, int NPK, int NDK, int EV, int EN, bool CLOSE, bool OPEN, bool WRITEBACK,
-          int CMP, int NCH, bool TL>
-__global__ __launch_bounds__(TL ? kTableBlock : kBlock) void k_force(Buffers b, int p, int q, int64_t n_slots,
-                                                                      PotArgs P, double dt, md_state st)
+          int CMP, int NCH, bool TL, bool STAGE>
+__global__ __launch_bounds__(TL ? kTableBlock : kBlock, STAGE && EN == 0 && NCH <= 4 ? 6 : 1) void k_force(
+    Buffers b, int p, int q, int64_t n_slots, PotArgs P, double dt, md_state st)
 {
     constexpr bool WSUM = EN == 4;
     constexpr int ENERGY = WSUM ? 1 : EN;
     extern __shared__ __align__(16) unsigned char smem[];
+    const int64_t t0 = logical_block() * blockDim.x, t = t0 + threadIdx.x;
+    const double4* __restrict__ pos = b.pos[p];
+    const Stage<true> S(smem, (int)t0);
+    double4 pi = make_double4(0.0, 0.0, 0.0, 0.0);
+    if (t < n_slots) {
+        pi = pos[t];
+        if (STAGE) S.put(threadIdx.x, pi);
+    }
     const Tabs<R> T = tables<R>(b);
     const R* tf = T.force;
     const R* te = T.energy;
     if (EV != EV_KNOTS && (SINGLE || TL)) {
         const int nf = (SINGLE ? 1 : P.ns * P.ns) * P.nbt * force_stride(EV);
-        R* s = reinterpret_cast<R*>(smem);
+        R* s = reinterpret_cast<R*>(smem + (STAGE ? S.kBytes : 0));
         lds_fill(s, tf, nf);
         if (ENERGY == 1) lds_fill(s + nf, te, (SINGLE ? 1 : P.ns * P.ns) * P.nbt * value_stride(EV));
-        __syncthreads();
         tf = s;
         te = s + nf;
     }
-    const int64_t t = global_thread();
+    if (STAGE || (EV != EV_KNOTS && (SINGLE || TL))) __syncthreads();
     if (t >= n_slots) return;
     const DevReplica& Rp = b.reps[uniform(b.rep_of_wave[t / kWave])];
     // slots past the replica's atoms: none in energy-sum mode, whose wavefront
@@ -418,8 +544,6 @@ __global__ __launch_bounds__(TL ? kTableBlock : kBlock) void k_force(Buffers b, 
     if (pad && !WSUM) return;
     const Box bx = load_box(Rp);
     const DevPotential& G = *b.pot;
-    const double4* __restrict__ pos = b.pos[p];
-    const double4 pi = pos[t];
     const int4 qi = CMP ? b.rec[1][t] : make_int4(0, 0, 0, 0);
     const int4 qb = compact_base(qi);
     const __amdgpu_buffer_rsrc_t rs = record_rsrc(b.rec[1], n_slots);
@@ -455,8 +579,8 @@ __global__ __launch_bounds__(TL ? kTableBlock : kBlock) void k_force(Buffers b, 
             for (int u = 0; u < NCH; ++u) {
                 e[u] = kb + u < n ? v[sb * NCH + u] : (int)t;
                 if (CMP) qs[u] = record_load(rs, e[u] & kIndexMask);
-                else ps[u] = pos[e[u] & kIndexMask];
             }
+            if (!CMP) S.template gather<STAGE, NCH>(pos, e, ps);
 #pragma unroll
             for (int u = 0; u < NCH; ++u) {
                 if (kb + u >= n) break;
@@ -719,21 +843,21 @@ __global__ void k_integrate_half(Buffers b, int p, int q, int64_t n_slots, PotAr
 
 }  // namespace
 
-template <typename R, bool S, int NP, int ND, int EV, int CMP, bool TL>
+template <typename R, bool S, int NP, int ND, int EV, int CMP, bool TL, bool STAGE>
 static void density_chunked(const Buffers& b, int p, int q, const KernelShape& k, const PotArgs& P, int energy,
                             size_t lds, hipStream_t s)
 {
     const int block = TL ? kTableBlock : kBlock;
     const dim3 grid((unsigned)((k.n_slots + block - 1) / block));
     if (k.nchunk == 2)
-        hipLaunchKernelGGL((k_density<R, S, NP, ND, EV, CMP, 2, TL>), grid, dim3(block), lds, s, b, p, q, k.n_slots,
-                           P, energy);
+        hipLaunchKernelGGL((k_density<R, S, NP, ND, EV, CMP, 2, TL, STAGE>), grid, dim3(block), lds, s, b, p, q,
+                           k.n_slots, P, energy);
     else if (k.nchunk == 8)
-        hipLaunchKernelGGL((k_density<R, S, NP, ND, EV, CMP, 8, TL>), grid, dim3(block), lds, s, b, p, q, k.n_slots,
-                           P, energy);
+        hipLaunchKernelGGL((k_density<R, S, NP, ND, EV, CMP, 8, TL, STAGE>), grid, dim3(block), lds, s, b, p, q,
+                           k.n_slots, P, energy);
     else
-        hipLaunchKernelGGL((k_density<R, S, NP, ND, EV, CMP, 4, TL>), grid, dim3(block), lds, s, b, p, q, k.n_slots,
-                           P, energy);
+        hipLaunchKernelGGL((k_density<R, S, NP, ND, EV, CMP, 4, TL, STAGE>), grid, dim3(block), lds, s, b, p, q,
+                           k.n_slots, P, energy);
 }
 
 template <typename R, bool S, int NP, int ND, int EV, int CMP>
@@ -750,11 +874,17 @@ static void density_tables(const Buffers& b, int p, int q, const KernelShape& k,
     const size_t bytes = EV != EV_KNOTS ? (size_t)(S ? 1 : P.ns * P.ns) * P.nbt * value_stride(EV) * sizeof(R) : 0;
     if constexpr (!S && EV != EV_KNOTS) {
         if (bytes <= (size_t)k.lds_limit) {
-            density_chunked<R, S, NP, ND, EV, CMP, true>(b, p, q, k, P, energy, bytes, s);
+            density_chunked<R, S, NP, ND, EV, CMP, true, false>(b, p, q, k, P, energy, bytes, s);
             return;
         }
     }
-    density_chunked<R, S, NP, ND, EV, CMP, false>(b, p, q, k, P, energy, S ? bytes : 0, s);
+    if constexpr (S && sizeof(R) == 8) {
+        if (k.stage && bytes + Stage<false>::kBytes <= (size_t)k.lds_limit) {
+            density_chunked<R, S, NP, ND, EV, CMP, false, true>(b, p, q, k, P, energy, bytes + Stage<false>::kBytes, s);
+            return;
+        }
+    }
+    density_chunked<R, S, NP, ND, EV, CMP, false, false>(b, p, q, k, P, energy, S ? bytes : 0, s);
 }
 
 template <typename R, bool S, int NP, int ND, int EV>
@@ -804,7 +934,7 @@ static void density_dispatch(const Buffers& b, int p, int q, const KernelShape& 
 // The neighbour chunk applies to the velocity-Verlet step kernels (with and
 // without energies) and to the plain force pass the autotuner times; the other
 // variants run once per call or per barostat step.
-template <typename R, bool S, int NP, int ND, int EV, int E, bool C, bool O, bool W, int CMP, bool TL>
+template <typename R, bool S, int NP, int ND, int EV, int E, bool C, bool O, bool W, int CMP, bool TL, bool STAGE>
 static void force_chunked(const Buffers& b, int p, int q, const KernelShape& k, const PotArgs& P, double dt_fs,
                           const md_state& st, size_t lds, hipStream_t s)
 {
@@ -813,17 +943,17 @@ static void force_chunked(const Buffers& b, int p, int q, const KernelShape& k, 
     constexpr bool step = ((E == 0 || E == 1 || E == 4) && C && O && !W) || (E == 0 && !C && !O && !W);
     if constexpr (step) {
         if (k.nchunk == 2) {
-            hipLaunchKernelGGL((k_force<R, S, NP, ND, EV, E, C, O, W, CMP, 2, TL>), grid, dim3(block), lds, s, b, p,
-                               q, k.n_slots, P, dt_fs, st);
+            hipLaunchKernelGGL((k_force<R, S, NP, ND, EV, E, C, O, W, CMP, 2, TL, STAGE>), grid, dim3(block), lds, s, b,
+                               p, q, k.n_slots, P, dt_fs, st);
             return;
         }
         if (k.nchunk == 8) {
-            hipLaunchKernelGGL((k_force<R, S, NP, ND, EV, E, C, O, W, CMP, 8, TL>), grid, dim3(block), lds, s, b, p,
-                               q, k.n_slots, P, dt_fs, st);
+            hipLaunchKernelGGL((k_force<R, S, NP, ND, EV, E, C, O, W, CMP, 8, TL, STAGE>), grid, dim3(block), lds, s, b,
+                               p, q, k.n_slots, P, dt_fs, st);
             return;
         }
     }
-    hipLaunchKernelGGL((k_force<R, S, NP, ND, EV, E, C, O, W, CMP, 4, TL>), grid, dim3(block), lds, s, b, p, q,
+    hipLaunchKernelGGL((k_force<R, S, NP, ND, EV, E, C, O, W, CMP, 4, TL, STAGE>), grid, dim3(block), lds, s, b, p, q,
                        k.n_slots, P, dt_fs, st);
 }
 
@@ -846,11 +976,18 @@ static void force_tables(const Buffers& b, int p, int q, const KernelShape& k, c
                                         : 0;
     if constexpr (!S && EV != EV_KNOTS) {
         if (bytes <= (size_t)k.lds_limit) {
-            force_chunked<R, S, NP, ND, EV, E, C, O, W, CMP, true>(b, p, q, k, P, dt_fs, st, bytes, s);
+            force_chunked<R, S, NP, ND, EV, E, C, O, W, CMP, true, false>(b, p, q, k, P, dt_fs, st, bytes, s);
             return;
         }
     }
-    force_chunked<R, S, NP, ND, EV, E, C, O, W, CMP, false>(b, p, q, k, P, dt_fs, st, S ? bytes : 0, s);
+    if constexpr (S && sizeof(R) == 8) {
+        if (k.stage && bytes + Stage<true>::kBytes <= (size_t)k.lds_limit) {
+            force_chunked<R, S, NP, ND, EV, E, C, O, W, CMP, false, true>(b, p, q, k, P, dt_fs, st,
+                                                                         bytes + Stage<true>::kBytes, s);
+            return;
+        }
+    }
+    force_chunked<R, S, NP, ND, EV, E, C, O, W, CMP, false, false>(b, p, q, k, P, dt_fs, st, S ? bytes : 0, s);
 }
 
 template <typename R, bool S, int NP, int ND, int EV, int E, bool C, bool O, bool W>

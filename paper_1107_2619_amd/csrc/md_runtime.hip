@@ -206,6 +206,8 @@ KernelShape shape(const md_ctx* c)
     k.nchunk = c->nchunk;
     // few atoms: up to two one-thread wavefronts per SIMD (see kernels_global.h)
     k.split = c->Np <= (int64_t)2 * kSimds * kWave;
+    // many atoms: beyond four wavefronts per SIMD the gathers bind, not their latency
+    k.stage = c->Np > (int64_t)4 * kSimds * kWave;
     k.list_types = c->single ? 0 : 1;
     return k;
 }

@@ -1,7 +1,8 @@
 """GPU tests of the split density and force kernels (the neighbours of 64 atoms
 dealt to the waves of a workgroup; systems of at most 131,072 slots): parity
 with the oracle where the deal has remainders, and bitwise agreement with the
-one-thread kernels, which larger systems use."""
+one-thread kernels, which larger systems use, and with their staged form (own
+records in LDS; one species in FP64 beyond 262,144 slots)."""
 import numpy as np
 import pytest
 
@@ -10,6 +11,7 @@ from tests.gpu_helpers import TOL, announce, energy_error, force_error
 
 pytestmark = pytest.mark.gpu
 SPLIT_SLOTS = 2 * 1024 * 64
+DIRECT_SLOTS = 4 * 1024 * 64
 
 
 @pytest.fixture(scope="module")
@@ -64,14 +66,15 @@ def test_split_rounds_against_oracle(md, orc, precision, skin, cap, potential):
     assert abs(en.pe[0] - ref.pe) <= TOL[precision]["energy"] * abs(ref.pe)
 
 
-@pytest.mark.parametrize("precision,potential", [("fp64", "fe_fs"), ("mixed", "fe_fs"), ("fp64", "fec_eam"),
-                                                 ("mixed", "fec_eam")])
-def test_split_equals_one_thread_bitwise(md, precision, potential):
+@pytest.mark.parametrize("precision,potential,slots", [
+    ("fp64", "fe_fs", SPLIT_SLOTS), ("mixed", "fe_fs", SPLIT_SLOTS), ("fp64", "fec_eam", SPLIT_SLOTS),
+    ("mixed", "fec_eam", SPLIT_SLOTS), ("fp64", "fe_fs", DIRECT_SLOTS)])
+def test_forms_agree_bitwise(md, precision, potential, slots):
     """The same replicas (128, 127, 64, 65 and 1 atoms) in a batch that fills the
-    largest split size and in one 64 slots larger: forces, energies, virial and
+    largest size of one form and in one 64 slots larger: forces, energies, virial and
     12 steps with energies are bitwise equal, so a replica does not depend on
     the size of its batch."""
-    announce(f"split against one thread {precision} {potential}")
+    announce(f"forms at {slots} slots {precision} {potential}")
     parts = []
     for k, n in enumerate((128, 127, 64, 65, 1)):
         p = _take(inputs.bcc_fe(4, seed=92 + k, pot_seed=92, displace=0.06, skin=0.8, potential=potential), n)
@@ -85,8 +88,8 @@ def test_split_equals_one_thread_bitwise(md, precision, potential):
     n = sum(p.n_atoms for p in parts)
     got = []
     for extra in (0, 1):
-        s = _batch(parts + [fill] * (SPLIT_SLOTS // 64 - used + extra))
-        assert sum((int(v) + 63) // 64 * 64 for v in np.diff(s.atom_offset)) == SPLIT_SLOTS + 64 * extra
+        s = _batch(parts + [fill] * (slots // 64 - used + extra))
+        assert sum((int(v) + 63) // 64 * 64 for v in np.diff(s.atom_offset)) == slots + 64 * extra
         sim = md.Simulation(s, precision=precision, energy_ring=8)
         sim.set_option(md.MD_OPT_ENERGY_EVERY, 2)
         sim.eam_forces()
