@@ -30,7 +30,7 @@ __device__ __forceinline__ int wave_run_add(int32_t* counter, int key)
 
 
 // ---------------------------------------------------------------------------
-// Rebuild stage 1 of 5: link cell of every atom, cell populations, and the skin
+// Rebuild stage 1 of 4: link cell of every atom, cell populations, and the skin
 // guard (net displacement since the previous build must stay below skin/2).
 // Every rebuild kernel takes `gate`: NULL for a build of all replicas, else
 // the automatic rebuild's flags, and then it leaves alone every replica r with
@@ -97,47 +97,116 @@ __global__ void k_bin(Buffers b, int p, int q, int64_t n_slots, double half_skin
         if (!replica_kept(b, gate, t)) bin_slot(b, p, q, t, half_skin2, check_skin);
 }
 
-// Rebuild stage 2: exclusive scan of cell populations in two phases (block scan, then
-// each block adds the sum of the block totals before it), shifted into slot numbering
+// Rebuild stage 2: exclusive scan of cell populations, shifted into slot numbering
 // with the per-cell replica shift.  The populations binned by stage 1 are taken over
-// (and their counters cleared for the next build); a kept replica's cells keep theirs.
+// (a kept replica's cells keep theirs).  One kernel where no replica has more than
+// kScanOnce cells, each block summing the populations before its own in the replica
+// of its first cell; beyond, where the blocks' readings grow with the square of the
+// cells, a block scan and a second kernel that adds the sums of the block totals
+// before each block.  One kernel against two: 2000 atoms 2.0 and 9.4 us, 256 liquids
+// 4.8 and 9.4, 138,000 cells of one replica 18.4 and 9.9.
 constexpr int kScanBlock = 1024;
+constexpr int32_t kScanOnce = 1 << 16;
 
-__device__ __forceinline__ int32_t block_exclusive_scan(int32_t v, int32_t* sh, int32_t& total)
+// Inclusive sums over the wavefront.
+__device__ __forceinline__ int32_t wave_inclusive_scan(int32_t v)
 {
-    // Hillis-Steele over the workgroup in LDS (1024 entries).
-    const int tid = threadIdx.x;
-    sh[tid] = v;
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);  // row_shr:1, 2, 4, 8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);  // row_bcast:15, 31
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);
+    return v;
+}
+
+// Exclusive sums over the workgroup, and its total.
+__device__ __forceinline__ int32_t block_exclusive_scan(int32_t v, int32_t& total)
+{
+    __shared__ int32_t part[kScanBlock / kWave];
+    const int32_t incl = wave_inclusive_scan(v);
+    if ((threadIdx.x & (kWave - 1)) == kWave - 1) part[threadIdx.x / kWave] = incl;
     __syncthreads();
-    for (int off = 1; off < kScanBlock; off <<= 1) {
-        const int32_t add = tid >= off ? sh[tid - off] : 0;
-        __syncthreads();
-        sh[tid] += add;
-        __syncthreads();
+    int32_t before = 0;
+    total = 0;
+#pragma unroll
+    for (int w = 0; w < kScanBlock / kWave; ++w) {
+        if (w < (int)(threadIdx.x / kWave)) before += part[w];
+        total += part[w];
     }
-    total = sh[kScanBlock - 1];
-    return sh[tid] - v;
+    return before + incl - v;
+}
+
+// Sum of a value over the workgroup.
+__device__ __forceinline__ int32_t block_sum(int32_t v)
+{
+    __shared__ int32_t sums[kScanBlock / kWave];
+    const int32_t incl = wave_inclusive_scan(v);
+    if ((threadIdx.x & (kWave - 1)) == kWave - 1) sums[threadIdx.x / kWave] = incl;
+    __syncthreads();
+    int32_t all = 0;
+#pragma unroll
+    for (int w = 0; w < kScanBlock / kWave; ++w) all += sums[w];
+    return all;
+}
+
+// Population of cell i in this build.
+__device__ __forceinline__ bool cell_kept(const Buffers& b, int64_t i, const int32_t* gate)
+{
+    if (!gate) return false;
+    const int r = b.cell_rep[i];
+    return r >= 0 && gate[1 + r] == 0;
+}
+
+__global__ __launch_bounds__(kScanBlock) void k_scan(Buffers b, int32_t n, const int32_t* __restrict__ gate)
+{
+    if (gate && gate[0] == 0) return;
+    // Cells before this block, in the replica of its first cell (those of the
+    // replicas before hold exactly their atoms; integers: any order is exact).
+    const int64_t first = (int64_t)blockIdx.x * kScanBlock;
+    const int r0 = b.cell_rep[first];
+    int32_t run = 0;
+    if (r0 >= 0) {
+        const DevReplica& R = b.reps[r0];
+        const int32_t* __restrict__ count = cell_kept(b, first, gate) ? b.cell_count : b.bin_count;
+        if (threadIdx.x == 0) run = R.atom_off;
+#pragma unroll 8
+        for (int64_t k = R.cell_off + threadIdx.x; k < first; k += kScanBlock) run += count[k];
+    }
+    const int64_t i = first + threadIdx.x;
+    int32_t v = 0;
+    if (i < n) {
+        if (cell_kept(b, i, gate)) {
+            v = b.cell_count[i];
+        } else {
+            v = b.bin_count[i];  // (other blocks read it too: cleared by stage 3)
+            b.cell_count[i] = v;
+            b.cell_cursor[i] = 0;
+        }
+    }
+    const int32_t before = block_sum(run);
+    int32_t total;
+    const int32_t ex = block_exclusive_scan(v, total);
+    if (i < n) b.cell_start[i] = before + ex + b.cell_shift[i];
+    if (gate && blockIdx.x == 0 && threadIdx.x == 0) atomicAdd(&b.flags[F_AUTO_BUILDS], 1);
 }
 
 __global__ __launch_bounds__(kScanBlock) void k_scan_local(Buffers b, int32_t n, const int32_t* __restrict__ gate)
 {
     if (gate && gate[0] == 0) return;
-    __shared__ int32_t sh[kScanBlock];
     const int64_t i = (int64_t)blockIdx.x * kScanBlock + threadIdx.x;
     int32_t v = 0;
     if (i < n) {
-        const int r = b.cell_rep[i];
-        if (gate && r >= 0 && gate[1 + r] == 0) {
+        if (cell_kept(b, i, gate)) {
             v = b.cell_count[i];
         } else {
             v = b.bin_count[i];
             b.cell_count[i] = v;
-            b.bin_count[i] = 0;
             b.cell_cursor[i] = 0;
         }
     }
     int32_t total;
-    const int32_t ex = block_exclusive_scan(v, sh, total);
+    const int32_t ex = block_exclusive_scan(v, total);
     if (i < n) b.cell_start[i] = ex;
     if (threadIdx.x == 0) b.scan_blocks[blockIdx.x] = total;
 }
@@ -145,29 +214,23 @@ __global__ __launch_bounds__(kScanBlock) void k_scan_local(Buffers b, int32_t n,
 __global__ __launch_bounds__(kScanBlock) void k_scan_add(Buffers b, int32_t n, const int32_t* __restrict__ gate)
 {
     if (gate && gate[0] == 0) return;
-    // the totals of the blocks before this one (integers: any order is exact)
-    __shared__ int32_t part[kScanBlock / kWave];
-    int32_t run = 0;
+    int32_t run = 0;  // the totals of the blocks before this one
     for (int k = threadIdx.x; k < (int)blockIdx.x; k += kScanBlock) run += b.scan_blocks[k];
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) run += __shfl_xor(run, off, kWave);
-    if ((threadIdx.x & (kWave - 1)) == 0) part[threadIdx.x / kWave] = run;
-    __syncthreads();
-    int32_t before = 0;
-#pragma unroll
-    for (int w = 0; w < kScanBlock / kWave; ++w) before += part[w];
+    const int32_t before = block_sum(run);
     const int64_t i = (int64_t)blockIdx.x * kScanBlock + threadIdx.x;
     if (i < n) b.cell_start[i] += before + b.cell_shift[i];
     if (gate && blockIdx.x == 0 && threadIdx.x == 0) atomicAdd(&b.flags[F_AUTO_BUILDS], 1);
 }
 
 // Rebuild stage 3: place every atom in its cell's slot range (arbitrary order within
-// the cell, fixed by the next kernel).
-__global__ void k_scatter(Buffers b, int64_t n_slots, const int32_t* __restrict__ gate)
+// the cell, fixed by the next kernel), and clear the bins for the next build (a kept
+// replica's are zero already).
+__global__ void k_scatter(Buffers b, int64_t n_slots, int32_t n_cells, const int32_t* __restrict__ gate)
 {
     if (gate && gate[0] == 0) return;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t t = global_thread(); t < n_slots; t += stride) {
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x, first = global_thread();
+    for (int64_t i = first; i < n_cells; i += stride) b.bin_count[i] = 0;
+    for (int64_t t = first; t < n_slots; t += stride) {
         if (replica_kept(b, gate, t)) continue;
         const int c = b.cell_of[t];
         const int k = wave_run_add(b.cell_cursor, c);
@@ -176,38 +239,26 @@ __global__ void k_scatter(Buffers b, int64_t n_slots, const int32_t* __restrict_
 }
 
 // Rebuild stage 4: order each cell's members by caller index, making the slot order
-// (and so every later floating-point sum) independent of atomics' timing.  Every
-// member counts the members of its cell with a smaller caller index (indices are
-// distinct): that count is its place in the cell, and its old slot goes there in
-// perm_sorted.
-__global__ void k_sort_cells(Buffers b, int q, int64_t n_slots, const int32_t* __restrict__ gate)
-{
-    if (gate && gate[0] == 0) return;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    const int32_t* __restrict__ id = b.id[q];
-    for (int64_t u = global_thread(); u < n_slots; u += stride) {
-        const int rep = uniform(b.rep_of_wave[u / kWave]);
-        if (gate && gate[1 + rep] == 0) continue;
-        const DevReplica& R = b.reps[rep];
-        if (u - R.slot_off >= R.n_atoms) continue;  // slots past the replica's atoms
-        const int32_t t = b.perm[u];
-        const int c = b.cell_of[t];
-        const int beg = b.cell_start[c], cnt = b.cell_count[c];
-        const int32_t key = id[t];
-        int place = 0;
-        for (int j = 0; j < cnt; ++j) place += id[b.perm[beg + j]] < key ? 1 : 0;
-        b.perm_sorted[beg + place] = t;
-    }
-}
-
-// Rebuild stage 5: gather the whole atom state into the new slot order.
+// (and so every later floating-point sum) independent of atomics' timing, and gather
+// the whole atom state into that order.  Every member counts the members of its cell
+// with a smaller caller index (indices are distinct): that count is its place in the
+// cell, where its state goes.  (One kernel: the order has no use of its own, and the
+// permuted slots are written and read once less; 1,013,760 atoms 15 + 48 -> 60 us, 2000 atoms 5.1 + 6.0 -> 8.6.)
 __device__ __forceinline__ void gather_slot(const Buffers& b, int p, int q, int64_t u, int compact)
 {
     const DevReplica& R = b.reps[uniform(b.rep_of_wave[u / kWave])];
     const int pn = p ^ 1, qn = q ^ 1;
     if (u - R.slot_off < R.n_atoms) {
-        const int32_t t = b.perm_sorted[u];
+        const int32_t t = b.perm[u];
+        const int cell = b.cell_of[t];
         const double3 x = load_xyz(b.pos[p], t);
+        const int beg = b.cell_start[cell], cnt = b.cell_count[cell];
+        const int32_t* __restrict__ id = b.id[q];
+        const int32_t key = id[t];
+        int place = 0;
+#pragma unroll 4
+        for (int j = 0; j < cnt; ++j) place += id[b.perm[beg + j]] < key ? 1 : 0;
+        const int64_t w = beg + place;  // the atom's new slot
         double xw[3] = {x.x, x.y, x.z};
         // re-wrap atoms that left the primary box on a periodic axis
         if (R.tri) {  // sheared cell: whole edge vectors, from the fractional coordinates
@@ -217,7 +268,7 @@ __device__ __forceinline__ void gather_slot(const Buffers& b, int p, int q, int6
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
                 k[a] = floor(f[a]);
-                b.img[qn][a][u] = b.img[q][a][t] + (int32_t)k[a];
+                b.img[qn][a][w] = b.img[q][a][t] + (int32_t)k[a];
             }
             double sh[3];
             lattice_shift(R, k[0], k[1], k[2], sh);
@@ -234,33 +285,33 @@ __device__ __forceinline__ void gather_slot(const Buffers& b, int p, int q, int6
                         n += (int32_t)s;
                     }
                 }
-                b.img[qn][a][u] = n;
+                b.img[qn][a][w] = n;
             }
         }
         const double4 x4 = make_double4(xw[0], xw[1], xw[2], 0.0);
-        b.pos[pn][u] = x4;
-        b.xbuild[u] = x4;
+        b.pos[pn][w] = x4;
+        b.xbuild[w] = x4;
         if (compact) {
             // the slot's link cell and its compact record (here, where every lane
             // holds an atom, and not in the list kernel, whose wavefronts own a
             // handful each)
-            const int cpk = b.cell_coord[b.cell_of[t]];
+            const int cpk = b.cell_coord[cell];
             const int c[3] = {cpk & 1023, (cpk >> 10) & 1023, cpk >> 20};
             int4 rq;
             if (!compact_coords(R, c, xw[0], xw[1], xw[2], rq)) atomicAdd(&b.flags[F_COMPACT], 1);
-            b.cellxyz[u] = make_int4(c[0], c[1], c[2], 0);
-            b.rec[0][u] = rq;
+            b.cellxyz[w] = make_int4(c[0], c[1], c[2], 0);
+            b.rec[0][w] = rq;
         }
 #pragma unroll
-        for (int a = 0; a < 3; ++a) b.vel[qn][a][u] = b.vel[q][a][t];
-        b.id[qn][u] = b.id[q][t];
-        b.type[qn][u] = b.type[q][t];
-        b.pwork[qn][u] = b.pwork[q][t];
+        for (int a = 0; a < 3; ++a) b.vel[qn][a][w] = b.vel[q][a][t];
+        b.id[qn][w] = b.id[q][t];
+        b.type[qn][w] = b.type[q][t];
+        b.pwork[qn][w] = b.pwork[q][t];
         if (b.acc[q][0]) {  // Gear integrator state travels with its atom
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
-                b.acc[qn][a][u] = b.acc[q][a][t];
-                b.jrk[qn][a][u] = b.jrk[q][a][t];
+                b.acc[qn][a][w] = b.acc[q][a][t];
+                b.jrk[qn][a][w] = b.jrk[q][a][t];
             }
         }
     } else {
@@ -821,10 +872,13 @@ void launch_rebuild(const Buffers& b, int p, int q, const KernelShape& k, double
     hipLaunchKernelGGL(k_bin, dim3(slot_blocks), dim3(kBlock), 0, s, b, p, q, k.n_slots,
                        half_skin2, half_skin2 >= 0.0 ? 1 : 0, gate);
     const int nb = (int)((k.n_cells + kScanBlock - 1) / kScanBlock);
-    hipLaunchKernelGGL(k_scan_local, dim3(nb), dim3(kScanBlock), 0, s, b, k.n_cells, gate);
-    hipLaunchKernelGGL(k_scan_add, dim3(nb), dim3(kScanBlock), 0, s, b, k.n_cells, gate);
-    hipLaunchKernelGGL(k_scatter, dim3(slot_blocks), dim3(kBlock), 0, s, b, k.n_slots, gate);
-    hipLaunchKernelGGL(k_sort_cells, dim3(slot_blocks), dim3(kBlock), 0, s, b, q, k.n_slots, gate);
+    if (k.rep_cells <= kScanOnce) {
+        hipLaunchKernelGGL(k_scan, dim3(nb), dim3(kScanBlock), 0, s, b, k.n_cells, gate);
+    } else {
+        hipLaunchKernelGGL(k_scan_local, dim3(nb), dim3(kScanBlock), 0, s, b, k.n_cells, gate);
+        hipLaunchKernelGGL(k_scan_add, dim3(nb), dim3(kScanBlock), 0, s, b, k.n_cells, gate);
+    }
+    hipLaunchKernelGGL(k_scatter, dim3(slot_blocks), dim3(kBlock), 0, s, b, k.n_slots, k.n_cells, gate);
     hipLaunchKernelGGL(k_gather, dim3(slot_blocks), dim3(kBlock), 0, s, b, p, q, k.n_slots, k.compact, gate);
 }
 

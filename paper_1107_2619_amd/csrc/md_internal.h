@@ -178,7 +178,6 @@ struct Buffers {
     uint8_t* ntype;       // type byte of every list entry, same layout (several species)
     double* wave_terms;   // [Np / 64][kEnergyTerms] per-wavefront energy sums (velocity-Verlet energy steps)
     uint16_t* nbr16;      // [Np][rowlen] rows of staging (LDS) indices (brick path)
-    int32_t* perm_sorted; // [Np] old slot of each new slot, cell members in caller-index order
     int32_t* brick_rep;   // [n_bricks] replica of each brick
     int4* brick_info;     // [n_bricks] own slot range [x, y) and halo atoms z at the last build
     int32_t* stage_src;   // [n_bricks][halo_cap] slot | shift code of each staging position
@@ -235,6 +234,7 @@ struct Buffers {
 struct KernelShape {
     int64_t n_slots;  // Np
     int32_t n_cells;
+    int32_t rep_cells;  // cells of the largest replica
     int32_t n_replicas;
     int32_t cap;
     int32_t npk, ndk; // knots per pair / density function

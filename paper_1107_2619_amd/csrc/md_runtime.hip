@@ -47,7 +47,7 @@ struct md_ctx {
     std::vector<float> tf32, te32, td32;
     // derived layout
     int64_t N = 0, Np = 0;
-    int32_t C = 0, C_alloc = 0, scan_nb = 0;
+    int32_t C = 0, C_alloc = 0, scan_nb = 0, rep_cells = 0;
     // brick path
     int32_t kernel_path = 1;  // 0 = LDS bricks, 1 = global gathers, 2 = LDS bricks with pairs once
     int32_t nchunk = 4;       // neighbour records in flight per thread (global kernels)
@@ -183,6 +183,7 @@ KernelShape shape(const md_ctx* c)
     KernelShape k;
     k.n_slots = c->Np;
     k.n_cells = c->C;
+    k.rep_cells = c->rep_cells;
     k.n_replicas = c->R;
     k.cap = c->cap;
     k.lanes = c->lanes > 0 ? std::min(c->lanes, 4) : 2;  // automatic: two lanes per atom
@@ -290,6 +291,8 @@ void choose_bricks(md_ctx* c, int32_t dims)
     c->halo_cap_max = (int32_t)std::max<int64_t>(64, std::min<int64_t>(max_cap, rec_cap));
     c->halo_cap = (int32_t)std::max<int64_t>(64, std::min<int64_t>(cap, c->halo_cap_max));
     c->C = (int32_t)std::max<int64_t>(cells, 1);
+    c->rep_cells = 0;
+    for (const DevReplica& D : c->reps) c->rep_cells = std::max(c->rep_cells, D.nbk[0] * D.nbk[1] * D.nbk[2] * D.cpb);
     c->cell_shift.assign(c->C_alloc, 0);
     c->cell_rep.assign(c->C_alloc, -1);
     for (int r = 0; r < c->R; ++r) {
@@ -528,7 +531,6 @@ void plan_workspace(md_ctx* c)
         c->tf64.size() * 8, c->te64.size() * 8, c->td64.size() * 8,  // tables FP64
         c->tf32.size() * 4, c->te32.size() * 4, c->td32.size() * 4,  // tables FP32
         (Np * (size_t)((c->cap + 7) / 8 * 8) + 64) * 2,     // nbr16 rows (+ one padding row for prefetches)
-        Np * 4,                                              // perm_sorted
         std::max<size_t>(max_bricks, 1) * 4,                 // brick_rep (bricks <= cells)
         std::max<size_t>(max_bricks, 1) * 16,                // brick_info
         stage_entries(c) * 4,                                // stage_src
@@ -615,7 +617,6 @@ void bind_buffers(md_ctx* c)
     at(b.tab_energy32);
     at(b.tab_dens32);
     at(b.nbr16);
-    at(b.perm_sorted);
     at(b.brick_rep);
     at(b.brick_info);
     at(b.stage_src);
