@@ -517,7 +517,11 @@ void plan_workspace(md_ctx* c)
         (size_t)c->R * sizeof(DevReplica),                   // reps
         sizeof(DevPotential),                                // pot
         Np * kEnergyTerms * 8,                               // eslot
+        // read back by md_energy in one copy: flags, energies, nh_state, pr_state
+        F_COUNT * 4,                                         // flags
         (size_t)c->R * kEnergySlots * 8,                     // energies
+        (size_t)c->R * 32,                                   // nh_state
+        c->pr ? (size_t)c->R * (c->tri ? kPrtState : kPrState) * 8 : 0,  // pr_state
         c->chunk_rep.size() * 4, c->chunk_off.size() * 4,     // reduction chunks
         c->chunk_rep.size() * kEnergySlots * 8,
         keep_f ? Np * 8 : 0,  // fhalf[3] (also the forces kept by the thermostat and the Gear steps)
@@ -525,9 +529,8 @@ void plan_workspace(md_ctx* c)
         keep_f ? Np * 8 : 0,
         c->nbr_mode == MD_NBR_HALF_ATOMIC ? Np * 8 : 0,     // rhalf
         c->nbr_mode == MD_NBR_HALF_ATOMIC ? Np * 8 : 0,     // ehalf
-        (size_t)c->R * 16, (size_t)c->R * 32,                // nh_param, nh_state
+        (size_t)c->R * 16,                                   // nh_param
         Np / kWave * 8,                                      // nh_partial
-        F_COUNT * 4,                                         // flags
         c->tf64.size() * 8, c->te64.size() * 8, c->td64.size() * 8,  // tables FP64
         c->tf32.size() * 4, c->te32.size() * 4, c->td32.size() * 4,  // tables FP32
         (Np * (size_t)((c->cap + 7) / 8 * 8) + 64) * 2,     // nbr16 rows (+ one padding row for prefetches)
@@ -547,7 +550,6 @@ void plan_workspace(md_ctx* c)
         gear, gear, gear, gear, gear, gear,                  // acc[2][3]
         gear, gear, gear, gear, gear, gear,                  // jrk[2][3]
         c->pr ? (size_t)c->R * 16 : 0,                       // pr_param
-        c->pr ? (size_t)c->R * (c->tri ? kPrtState : kPrState) * 8 : 0,  // pr_state
         c->pr ? Np / kWave * (c->tri ? 12 : 6) * 8 : 0,      // pr_partial
         (size_t)c->ring_len * c->R * kEnergySlots * 8,       // ering
         16,                                                  // ering_count, ticket
@@ -599,7 +601,10 @@ void bind_buffers(md_ctx* c)
     at(b.reps);
     at(b.pot);
     at(b.eslot);
+    at(b.flags);
     at(b.energies);
+    at(b.nh_state);
+    at(b.pr_state);
     at(b.chunk_rep);
     at(b.chunk_off);
     at(b.chunk_partial);
@@ -607,9 +612,7 @@ void bind_buffers(md_ctx* c)
     at(b.rhalf);
     at(b.ehalf);
     at(b.nh_param);
-    at(b.nh_state);
     at(b.nh_partial);
-    at(b.flags);
     at(b.tab_force64);
     at(b.tab_energy64);
     at(b.tab_dens64);
@@ -639,7 +642,6 @@ void bind_buffers(md_ctx* c)
         for (int k = 0; k < 2; ++k)
             for (int a = 0; a < 3; ++a) b.acc[k][a] = b.jrk[k][a] = nullptr;
     at(b.pr_param);
-    at(b.pr_state);
     at(b.pr_partial);
     at(b.ering);
     at(b.ering_count);
@@ -1618,22 +1620,27 @@ int md_energy(md_ctx* c, md_energies* out, void* stream)
     if (!c || !out) return fail(c, MD_ERR_ARG, "md_energy: NULL argument");
     if (!c->bound) return fail(c, MD_ERR_STATE, "md_energy: call md_bind first");
     hipStream_t s = as_stream(stream);
-    std::vector<double> e((size_t)c->R * kEnergySlots, 0.0);
-    int32_t flags[F_COUNT] = {};
-    if (!hip_ok(c, hipStreamSynchronize(s), "md_energy sync")) return MD_ERR_DEVICE;
-    collect_times(c);
-    if (!hip_ok(c, hipMemcpy(flags, c->buf.flags, sizeof flags, hipMemcpyDeviceToHost), "md_energy flags")) return MD_ERR_DEVICE;
-    if (c->have_energy && !hip_ok(c, hipMemcpy(e.data(), c->buf.energies, e.size() * 8, hipMemcpyDeviceToHost), "md_energy copy"))
-        return MD_ERR_DEVICE;
-    c->max_count = flags[F_MAX_COUNT];
-    c->auto_builds = flags[F_AUTO_BUILDS];
-    std::vector<double> nh((size_t)c->R * 4, 0.0);
-    if (c->nvt && !hip_ok(c, hipMemcpy(nh.data(), c->buf.nh_state, nh.size() * 8, hipMemcpyDeviceToHost), "md_energy thermostat"))
-        return MD_ERR_DEVICE;
+    std::vector<double> e((size_t)c->R * kEnergySlots, 0.0), nh((size_t)c->R * 4, 0.0);
     const int nps = c->tri ? kPrtState : kPrState;
     std::vector<double> pr((size_t)c->R * nps, 0.0);
-    if (c->pr && !hip_ok(c, hipMemcpy(pr.data(), c->buf.pr_state, pr.size() * 8, hipMemcpyDeviceToHost), "md_energy barostat"))
+    int32_t flags[F_COUNT] = {};
+    // flags, energies, thermostat and barostat states lie one behind the other in
+    // the workspace: one copy, which also waits for the stream (each takes ~10 us)
+    const char* from = reinterpret_cast<const char*>(c->buf.flags);
+    auto at = [&](const void* p) { return (size_t)(static_cast<const char*>(p) - from); };
+    const size_t bytes = c->pr     ? at(c->buf.pr_state) + pr.size() * 8
+                         : c->nvt  ? at(c->buf.nh_state) + nh.size() * 8
+                                   : at(c->buf.energies) + e.size() * 8;
+    std::vector<char> got(bytes);
+    if (!hip_ok(c, hipMemcpyWithStream(got.data(), from, bytes, hipMemcpyDeviceToHost, s), "md_energy copy"))
         return MD_ERR_DEVICE;
+    collect_times(c);
+    std::memcpy(flags, got.data(), sizeof flags);
+    if (c->have_energy) std::memcpy(e.data(), got.data() + at(c->buf.energies), e.size() * 8);
+    if (c->nvt) std::memcpy(nh.data(), got.data() + at(c->buf.nh_state), nh.size() * 8);
+    if (c->pr) std::memcpy(pr.data(), got.data() + at(c->buf.pr_state), pr.size() * 8);
+    c->max_count = flags[F_MAX_COUNT];
+    c->auto_builds = flags[F_AUTO_BUILDS];
     for (int r = 0; r < c->R; ++r) fill_energies(c, r, e.data() + (size_t)r * kEnergySlots, nh, pr, c->step, out[r]);
     // a non-finite state first: it also trips the displacement checks
     for (int r = 0; r < c->R; ++r) {
@@ -1683,16 +1690,19 @@ int md_energy_history(md_ctx* c, md_energies* out, int64_t max_entries, int64_t*
     c->ring_read = std::max(c->ring_read, pushed - c->ring_len);
     const int64_t n = std::min(pushed - c->ring_read, max_entries);
     const size_t per = (size_t)c->R * kEnergySlots;
-    std::vector<double> v(per);
-    const std::vector<double> none;
-    for (int64_t j = 0; j < n; ++j) {
-        const int64_t i = c->ring_read + j;
-        if (!hip_ok(c, hipMemcpy(v.data(), c->buf.ering + (size_t)(i % c->ring_len) * per, per * 8,
+    std::vector<double> v(per * (size_t)std::max<int64_t>(n, 0));
+    for (int64_t j = 0; j < n;) {  // the ring's entries in at most two pieces
+        const int64_t i = (c->ring_read + j) % c->ring_len, k = std::min(n - j, c->ring_len - i);
+        if (!hip_ok(c, hipMemcpy(v.data() + (size_t)j * per, c->buf.ering + (size_t)i * per, (size_t)k * per * 8,
                                  hipMemcpyDeviceToHost), "md_energy_history copy"))
             return MD_ERR_DEVICE;
-        for (int r = 0; r < c->R; ++r)
-            fill_energies(c, r, v.data() + (size_t)r * kEnergySlots, none, none, c->ring_steps[i], out[j * c->R + r]);
+        j += k;
     }
+    const std::vector<double> none;
+    for (int64_t j = 0; j < n; ++j)
+        for (int r = 0; r < c->R; ++r)
+            fill_energies(c, r, v.data() + (size_t)j * per + (size_t)r * kEnergySlots, none, none,
+                          c->ring_steps[c->ring_read + j], out[j * c->R + r]);
     c->ring_read += n;
     *n_out = n;
     return MD_OK;

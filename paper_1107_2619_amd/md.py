@@ -94,6 +94,8 @@ class _Energies(ctypes.Structure):
     ]
 
 
+_ENERGIES_DTYPE = np.dtype(_Energies)  # its fields as a structured array
+
 _lib = None
 
 
@@ -257,6 +259,14 @@ class Energies:
     h: np.ndarray          # [R, 3, 3] box matrices (edge vectors as columns), A
 
 
+def _energies_of(rec) -> Energies:
+    """Energies from the records of one state (a structured array, one per replica)."""
+    g = lambda name: rec[name].copy()  # noqa: E731
+    return Energies(g("pe"), g("ke"), g("temperature"), g("pressure_gpa"), g("volume"), g("piston_work"), g("virial"),
+                    int(rec["step"][0]), g("n_atoms"), g("n_mobile"), g("nh_pi"), g("nh_energy"), g("box"),
+                    g("pr_energy"), g("h").reshape(len(rec), 3, 3))
+
+
 class Simulation:
     """Device state (torch tensors) bound to a Context built from ``system``
     (an ``inputs.System``); the keyword options are those of ``Context``."""
@@ -348,30 +358,19 @@ class Simulation:
         R = self.ctx.n_replicas
         out = (_Energies * R)()
         self.ctx._check(self.ctx.lib.md_energy(self.ctx.handle, out, self.stream))
-        g = lambda name: np.array([getattr(o, name) for o in out])  # noqa: E731
-        return Energies(g("pe"), g("ke"), g("temperature"), g("pressure_gpa"), g("volume"), g("piston_work"),
-                        np.array([list(o.virial) for o in out]), int(out[0].step), g("n_atoms"), g("n_mobile"),
-                        g("nh_pi"), g("nh_energy"), np.array([list(o.box) for o in out]), g("pr_energy"),
-                        np.array([list(o.h) for o in out]).reshape(R, 3, 3))
+        return _energies_of(np.frombuffer(out, _ENERGIES_DTYPE))
 
     def energy_history(self, max_entries=10000) -> list:
         """Per-step energies appended since the last call (md_energy_history):
         a list of Energies, one per sampled step, oldest first."""
         R = self.ctx.n_replicas
+        max_entries = min(int(max_entries), self.get_option(MD_OPT_ENERGY_RING))  # it holds no more
         out = (_Energies * (R * max_entries))()
         n = ctypes.c_int64(0)
         self.ctx._check(self.ctx.lib.md_energy_history(self.ctx.handle, out, int(max_entries), ctypes.byref(n),
                                                        self.stream))
-        res = []
-        for j in range(n.value):
-            rec = out[j * R:(j + 1) * R]
-            g = lambda name: np.array([getattr(o, name) for o in rec])  # noqa: E731
-            res.append(Energies(g("pe"), g("ke"), g("temperature"), g("pressure_gpa"), g("volume"),
-                                g("piston_work"), np.array([list(o.virial) for o in rec]), int(rec[0].step),
-                                g("n_atoms"), g("n_mobile"), g("nh_pi"), g("nh_energy"),
-                                np.array([list(o.box) for o in rec]), g("pr_energy"),
-                                np.array([list(o.h) for o in rec]).reshape(R, 3, 3)))
-        return res
+        rec = np.frombuffer(out, _ENERGIES_DTYPE) if n.value else None
+        return [_energies_of(rec[j * R:(j + 1) * R]) for j in range(n.value)]
 
     def msd(self):
         """(msd [R, n_species] A^2, count [R, n_species]): mean square displacement
