@@ -764,9 +764,10 @@ void launch_force(const Buffers& b, int p, int q, const KernelShape& k, const Po
 }
 
 void launch_nh_update(const Buffers& b, int q, const KernelShape& k, const PotArgs& P, int halves, double dt_fs,
-                      hipStream_t s)
+                      int summed, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_nh_ke_waves, dim3(blocks_for(k.n_slots)), dim3(kBlock), 0, s, b, q, k.n_slots, P);
+    if (!summed)
+        hipLaunchKernelGGL(k_nh_ke_waves, dim3(blocks_for(k.n_slots)), dim3(kBlock), 0, s, b, q, k.n_slots, P);
     if (k.chunked && k.n_chunks > 0)
         hipLaunchKernelGGL(k_chunk_sums<1>, dim3(k.n_chunks), dim3(kWave), 0, s, b, b.nh_partial);
     if (k.n_replicas > 0)
@@ -788,9 +789,10 @@ void launch_pr_chunk_sums(const Buffers& b, const KernelShape& k, int n_terms, h
 }
 
 void launch_pr_update(const Buffers& b, int q, const KernelShape& k, const PotArgs& P, int close, int open,
-                      double dt_fs, double rlist, double strain_tol, int nvt, hipStream_t s)
+                      double dt_fs, double rlist, double strain_tol, int nvt, int summed, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_pr_tensor_waves, dim3(blocks_for(k.n_slots)), dim3(kBlock), 0, s, b, q, k.n_slots, P);
+    if (!summed)
+        hipLaunchKernelGGL(k_pr_tensor_waves, dim3(blocks_for(k.n_slots)), dim3(kBlock), 0, s, b, q, k.n_slots, P);
     launch_pr_chunk_sums(b, k, 6, s);
     if (k.n_replicas > 0)
         hipLaunchKernelGGL(k_pr_update, dim3(k.n_replicas), dim3(kBlock), 0, s, b, close, open, dt_fs, rlist,

@@ -391,9 +391,10 @@ __global__ void k_prt_close_scale(Buffers b, int q, int64_t n_slots, PotArgs P, 
 }  // namespace
 
 void launch_prt_update(const Buffers& b, int q, const KernelShape& k, const PotArgs& P, int close, int open,
-                       double dt_fs, double rlist, double strain_tol, int nvt, hipStream_t s)
+                       double dt_fs, double rlist, double strain_tol, int nvt, int summed, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_prt_tensor_waves, dim3(blocks_for(k.n_slots)), dim3(kBlock), 0, s, b, q, k.n_slots, P);
+    if (!summed)
+        hipLaunchKernelGGL(k_prt_tensor_waves, dim3(blocks_for(k.n_slots)), dim3(kBlock), 0, s, b, q, k.n_slots, P);
     launch_pr_chunk_sums(b, k, 12, s);
     if (k.n_replicas > 0)
         hipLaunchKernelGGL(k_prt_update, dim3(k.n_replicas), dim3(kBlock), 0, s, b, close, open, dt_fs, rlist,

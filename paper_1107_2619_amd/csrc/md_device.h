@@ -533,12 +533,13 @@ __device__ __forceinline__ void accumulate(PairAcc& A, double s, double dx, doub
 // steps the atom's energy terms go to its slot of `eslot`; with WRITEBACK the
 // final state returns to the caller's arrays (caller order, unwrapped).
 //
-// WSUM: the energy terms go to `wv` for a wavefront sum instead of `eslot`.
+// WSUM: the energy terms go to `wv` for a wavefront sum instead of `eslot` (of a
+// barostat step none: its caller sums the virial itself).  vout: the velocity.
 template <bool SINGLE, int ENERGY, bool CLOSE, bool OPEN, bool WRITEBACK, bool WSUM = false>
 __device__ __forceinline__ void atom_epilogue(const Buffers& b, int p, int q, int64_t t, int64_t n_slots,
                                               const DevReplica& Rp, const PotArgs& P, const DevPotential& G,
                                               double dt, const md_state& st, const double4& pi, uint8_t ti,
-                                              const PairAcc& A, double* wv = nullptr)
+                                              const PairAcc& A, double* wv = nullptr, double* vout = nullptr)
 {
     const int si = ti & 0x3F;
     const bool rigid_i = ti & kRigidBit;
@@ -578,6 +579,9 @@ __device__ __forceinline__ void atom_epilogue(const Buffers& b, int p, int q, in
             for (int a = 0; a < 3; ++a) b.vel[q][a][t] = v[a];
         }
     }
+    if (vout)
+#pragma unroll
+        for (int a = 0; a < 3; ++a) vout[a] = v[a];
     if (OPEN) {
         double* dst = reinterpret_cast<double*>(b.pos[p ^ 1] + t);
         *reinterpret_cast<double2*>(dst) = make_double2(xn[0], xn[1]);
@@ -593,7 +597,7 @@ __device__ __forceinline__ void atom_epilogue(const Buffers& b, int p, int q, in
             if (WSUM) wv[k] = vals[k];
             else b.eslot[(int64_t)k * n_slots + t] = vals[k];
         }
-    } else if (ENERGY == 2 || ENERGY == 3) {  // barostat steps: the virial diagonal, or the whole tensor
+    } else if ((ENERGY == 2 || ENERGY == 3) && !WSUM) {  // barostat steps: the virial diagonal, or the whole tensor
 #pragma unroll
         for (int k = 0; k < (ENERGY == 3 ? 6 : 3); ++k) b.eslot[(int64_t)(E_W0 + k) * n_slots + t] = A.w[k];
     }

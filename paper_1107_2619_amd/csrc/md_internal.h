@@ -302,8 +302,9 @@ void launch_reduce_waves(const Buffers& b, const KernelShape& k, double virial_s
 // Nose-Hoover thermostat: kinetic energy per replica and `halves` thermostat
 // half steps of length dt/2 (launch_nh_update); then either the scaled opening
 // kick and drift (launch_nh_open) or the final scaling (launch_nh_scale).
+// summed: the force pass left its per-wavefront sums (also for the barostats below).
 void launch_nh_update(const Buffers& b, int q, const KernelShape& k, const PotArgs& P, int halves, double dt_fs,
-                      hipStream_t s);
+                      int summed, hipStream_t s);
 // scaled = 1: the thermostat's velocity scale first (NVT); 0: the plain
 // opening kick and drift from the kept forces (an md_step call continuing
 // from the last one).
@@ -322,7 +323,7 @@ void launch_gear_correct(const Buffers& b, int p, int q, const KernelShape& k, c
 // its drift, [12,15) h phi(u) L'/L of its drift, [15,18) closing velocity scale.
 constexpr int kPrState = 20;
 void launch_pr_update(const Buffers& b, int q, const KernelShape& k, const PotArgs& P, int close, int open,
-                      double dt_fs, double rlist, double strain_tol, int nvt, hipStream_t s);
+                      double dt_fs, double rlist, double strain_tol, int nvt, int summed, hipStream_t s);
 void launch_pr_open(const Buffers& b, int p, int q, const KernelShape& k, const PotArgs& P, double dt_fs,
                     hipStream_t s);
 void launch_pr_close_scale(const Buffers& b, int q, const KernelShape& k, const PotArgs& P, const md_state& st,
@@ -338,7 +339,7 @@ void launch_pr_chunk_sums(const Buffers& b, const KernelShape& k, int n_terms, h
 // [45,54) the velocity term of its drift, [54,63) closing velocity map.
 constexpr int kPrtState = 64;
 void launch_prt_update(const Buffers& b, int q, const KernelShape& k, const PotArgs& P, int close, int open,
-                       double dt_fs, double rlist, double strain_tol, int nvt, hipStream_t s);
+                       double dt_fs, double rlist, double strain_tol, int nvt, int summed, hipStream_t s);
 void launch_prt_open(const Buffers& b, int p, int q, const KernelShape& k, const PotArgs& P, double dt_fs,
                      hipStream_t s);
 void launch_prt_close_scale(const Buffers& b, int q, const KernelShape& k, const PotArgs& P, const md_state& st,

@@ -834,11 +834,11 @@ void forces(md_ctx* c, ForceFlags fl, hipStream_t s, bool reduce = true)
 
 // Thermostatted step boundary: kinetic energy, `halves` thermostat half steps,
 // then the scaled opening kick and drift (which moves the positions to p^1).
-void nh_boundary(md_ctx* c, int halves, hipStream_t s)
+void nh_boundary(md_ctx* c, int halves, bool summed, hipStream_t s)
 {
     const KernelShape k = shape(c);
     Timed tm(c, MD_KT_FORCE, s);
-    launch_nh_update(c->buf, c->q, k, c->args, halves, c->dt_fs, s);
+    launch_nh_update(c->buf, c->q, k, c->args, halves, c->dt_fs, summed, s);
     launch_nh_open(c->buf, c->p, c->q, k, c->args, c->dt_fs, 1, s);
     c->p ^= 1;
 }
@@ -862,19 +862,19 @@ int64_t graph_period(const md_ctx* c) { return c->auto_rebuild ? kAutoGraphSteps
 // Barostat step boundary: the stress tensor, the box half kicks (closing,
 // opening or both), and with `open` the box drift and the particles' opening
 // friction, kick and drift (into pos[p^1]).
-void pr_boundary(md_ctx* c, int close, int open, hipStream_t s)
+void pr_boundary(md_ctx* c, int close, int open, bool summed, hipStream_t s)
 {
     const KernelShape k = shape(c);
     Timed tm(c, MD_KT_FORCE, s);
     if (c->tri) {
-        launch_prt_update(c->buf, c->q, k, c->args, close, open, c->dt_fs, c->rlist, 0.2 * c->skin, c->nvt, s);
+        launch_prt_update(c->buf, c->q, k, c->args, close, open, c->dt_fs, c->rlist, 0.2 * c->skin, c->nvt, summed, s);
         if (open) {
             launch_prt_open(c->buf, c->p, c->q, k, c->args, c->dt_fs, s);
             c->p ^= 1;
         }
         return;
     }
-    launch_pr_update(c->buf, c->q, k, c->args, close, open, c->dt_fs, c->rlist, 0.2 * c->skin, c->nvt, s);
+    launch_pr_update(c->buf, c->q, k, c->args, close, open, c->dt_fs, c->rlist, 0.2 * c->skin, c->nvt, summed, s);
     if (open) {
         launch_pr_open(c->buf, c->p, c->q, k, c->args, c->dt_fs, s);
         c->p ^= 1;
@@ -914,10 +914,10 @@ void middle_steps(md_ctx* c, int64_t n, hipStream_t s)
         if (c->pr) {
             // closing kick and the virial (the whole tensor for a box matrix), forces kept
             forces(c, ForceFlags{c->tri ? 3 : 2, 1, 0, 0}, s, false);
-            pr_boundary(c, 1, 1, s);
+            pr_boundary(c, 1, 1, true, s);  // (the global kernels always serve the barostat)
         } else if (c->nvt) {
             forces(c, ForceFlags{0, 1, 0, 0}, s);  // closing kick, forces kept
-            nh_boundary(c, 2, s);
+            nh_boundary(c, 2, !shape(c).brick && c->nbr_mode == MD_NBR_FULL, s);
         } else {
             const int e = c->energy_every > 0 && c->step % c->energy_every == 0 ? 1 : 0;
             forces(c, ForceFlags{e, 1, 1, 0}, s);
@@ -1539,7 +1539,7 @@ int md_step(md_ctx* c, int32_t nsteps, void* stream)
     else if (!resume && c->auto_rebuild) check_loaded(c, s);
     if (resume) {
         if (c->nvt) {
-            nh_boundary(c, 1, s);  // thermostat half step, opening kick, drift
+            nh_boundary(c, 1, false, s);  // thermostat half step, opening kick, drift
         } else {
             Timed tm(c, MD_KT_FORCE, s);
             launch_nh_open(c->buf, c->p, c->q, shape(c), c->args, c->dt_fs, 0, s);  // opening kick, drift
@@ -1558,10 +1558,10 @@ int md_step(md_ctx* c, int32_t nsteps, void* stream)
         c->p ^= 1;
     } else if (c->pr) {
         forces(c, ForceFlags{c->tri ? 3 : 2, 0, 0, 0}, s, false);  // f(x0) and the virial
-        pr_boundary(c, 0, 1, s);                      // box half kick and drift, opening kick and drift
+        pr_boundary(c, 0, 1, false, s);                      // box half kick and drift, opening kick and drift
     } else if (c->nvt) {
         forces(c, ForceFlags{0, 0, 0, 0}, s);  // f(x0) kept for the kick
-        nh_boundary(c, 1, s);                  // thermostat half step, opening kick, drift
+        nh_boundary(c, 1, false, s);                  // thermostat half step, opening kick, drift
     } else {
         forces(c, ForceFlags{0, 0, 1, 0}, s);  // f(x0), opening half kick, drift
     }
@@ -1590,10 +1590,10 @@ int md_step(md_ctx* c, int32_t nsteps, void* stream)
         {
             Timed tm(c, MD_KT_FORCE, s);
             if (c->tri) {
-                launch_prt_update(c->buf, c->q, k, c->args, 1, 0, c->dt_fs, c->rlist, 0.2 * c->skin, c->nvt, s);
+                launch_prt_update(c->buf, c->q, k, c->args, 1, 0, c->dt_fs, c->rlist, 0.2 * c->skin, c->nvt, 0, s);
                 launch_prt_close_scale(c->buf, c->q, k, c->args, c->st, s);
             } else {
-                launch_pr_update(c->buf, c->q, k, c->args, 1, 0, c->dt_fs, c->rlist, 0.2 * c->skin, c->nvt, s);  // closing halves
+                launch_pr_update(c->buf, c->q, k, c->args, 1, 0, c->dt_fs, c->rlist, 0.2 * c->skin, c->nvt, 0, s);  // closing halves
                 launch_pr_close_scale(c->buf, c->q, k, c->args, c->st, s);
             }
         }
@@ -1603,7 +1603,7 @@ int md_step(md_ctx* c, int32_t nsteps, void* stream)
         const KernelShape k = shape(c);
         {
             Timed tm(c, MD_KT_FORCE, s);
-            launch_nh_update(c->buf, c->q, k, c->args, 1, c->dt_fs, s);  // closing thermostat half step
+            launch_nh_update(c->buf, c->q, k, c->args, 1, c->dt_fs, 0, s);  // closing thermostat half step
             launch_nh_scale(c->buf, c->q, k, c->st, 1, s);
         }
         reduce_energies(c, k, s);
