@@ -309,9 +309,18 @@ __global__ __launch_bounds__(TL ? kTableBlock : kBlock) void k_density(Buffers b
     const int64_t t0 = logical_block() * blockDim.x, t = t0 + threadIdx.x;
     const double4* __restrict__ pos = b.pos[p];
     const Stage<false> S(smem, (int)t0);
+    // what the loop starts from is read before the tables, whose copy covers it
     double3 xi = make_double3(0.0, 0.0, 0.0);
-    if (!CMP && t < n_slots) {
-        xi = load_xyz(pos, t);
+    int4 qi = make_int4(0, 0, 0, 0);
+    int rep = 0, si = 0, n = 0;
+    if (t < n_slots) {
+        rep = b.rep_of_wave[t / kWave];
+        // the row's inner entries: the others lie beyond every density cutoff until the
+        // next build (1,013,760 atoms, 17 of 28 entries: FP64 72 -> 59 us, mixed 56 -> 42)
+        n = b.ninner[t];
+        si = b.type[q][t] & 0x3F;
+        if (CMP) qi = b.rec[0][t];
+        else xi = load_xyz(pos, t);
         if (STAGE) S.put(threadIdx.x, xi);
     }
     const R* tab = tables<R>(b).dens;
@@ -322,17 +331,12 @@ __global__ __launch_bounds__(TL ? kTableBlock : kBlock) void k_density(Buffers b
     }
     if (STAGE || (EV != EV_KNOTS && (SINGLE || TL))) __syncthreads();
     if (t >= n_slots) return;
-    const DevReplica& Rp = b.reps[uniform(b.rep_of_wave[t / kWave])];
+    const DevReplica& Rp = b.reps[uniform(rep)];
     if (t - Rp.slot_off >= Rp.n_atoms) return;
     const Box bx = load_box(Rp);
     const DevPotential& G = *b.pot;
-    const int4 qi = CMP ? b.rec[0][t] : make_int4(0, 0, 0, 0);
     const int4 qb = compact_base(qi);
     const __amdgpu_buffer_rsrc_t rs = record_rsrc(b.rec[0], n_slots);
-    const int si = b.type[q][t] & 0x3F;
-    // the row's inner entries: the others lie beyond every density cutoff until the
-    // next build (1,013,760 atoms, 17 of 28 entries: FP64 72 -> 59 us, mixed 56 -> 42)
-    const int n = b.ninner[t];
     double rho = 0.0;
     constexpr int GR = NCH >= kChunk ? NCH / kChunk : 1;  // list groups per iteration
     constexpr int SUB = NCH >= kChunk ? 1 : kChunk / NCH;  // record batches per group
@@ -566,9 +570,17 @@ __global__ __launch_bounds__(TL ? kTableBlock : kBlock, STAGE && EN == 0 && NCH 
     const int64_t t0 = logical_block() * blockDim.x, t = t0 + threadIdx.x;
     const double4* __restrict__ pos = b.pos[p];
     const Stage<true> S(smem, (int)t0);
+    // what the loop starts from is read before the tables, whose copy covers it
     double4 pi = make_double4(0.0, 0.0, 0.0, 0.0);
+    int4 qi = make_int4(0, 0, 0, 0);
+    int rep = 0, n_row = 0;
+    uint8_t ti = 0;
     if (t < n_slots) {
-        pi = pos[t];
+        rep = b.rep_of_wave[t / kWave];
+        n_row = b.ncount[t];
+        ti = b.type[q][t];
+        if (CMP) qi = b.rec[1][t];
+        else pi = pos[t];
         if (STAGE) S.put(threadIdx.x, pi);
     }
     const Tabs<R> T = tables<R>(b);
@@ -584,18 +596,16 @@ __global__ __launch_bounds__(TL ? kTableBlock : kBlock, STAGE && EN == 0 && NCH 
     }
     if (STAGE || (EV != EV_KNOTS && (SINGLE || TL))) __syncthreads();
     if (t >= n_slots) return;
-    const DevReplica& Rp = b.reps[uniform(b.rep_of_wave[t / kWave])];
+    const DevReplica& Rp = b.reps[uniform(rep)];
     // slots past the replica's atoms leave, but for wavefront sums, which need every
     // lane (those lanes add zeros)
     const bool pad = t - Rp.slot_off >= Rp.n_atoms;
     if (pad && !WSUM && !boundary_sums<EN, CLOSE, OPEN, WRITEBACK>()) return;
     const Box bx = load_box(Rp);
     const DevPotential& G = *b.pot;
-    const int4 qi = CMP ? b.rec[1][t] : make_int4(0, 0, 0, 0);
     const int4 qb = compact_base(qi);
     const __amdgpu_buffer_rsrc_t rs = record_rsrc(b.rec[1], n_slots);
-    const uint8_t ti = b.type[q][t];
-    const int n = pad ? 0 : b.ncount[t];
+    const int n = pad ? 0 : n_row;
     const R fpi = CMP ? (R)__int_as_float(qi.w) : (R)pi.w;
     PairAcc A;
     constexpr int GR = NCH >= kChunk ? NCH / kChunk : 1;  // list groups per iteration
@@ -640,6 +650,7 @@ __global__ __launch_bounds__(TL ? kTableBlock : kBlock, STAGE && EN == 0 && NCH 
 #pragma unroll
         for (int g = 0; g < GR; ++g) add_group<ENERGY>(A, sum[g]);
     }
+    if (CMP) pi = pos[t];  // (the loop runs on the compact record)
     force_epilogue<SINGLE, EN, CLOSE, OPEN, WRITEBACK, CMP>(b, p, q, t, n_slots, Rp, P, G, dt, st, pi, ti, A, pad);
 }
 
