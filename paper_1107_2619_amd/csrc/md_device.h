@@ -416,9 +416,8 @@ __device__ __forceinline__ R density_term(const PotArgs& P, const DevPotential& 
 
 // g_ij = phi'_{ij}(r) + F'_i rho'_{ij}(r) + F'_j rho'_{ji}(r) and, on energy
 // steps, phi_{ij}(r).  Tables: tf = [ns*ns][nbt][kForceStride] derivative quadratics,
-// te = [ns*ns][nbt][4] value cubics.  DENS = false: a pair beyond every density
-// cutoff, whose rho' terms vanish (the caller knows it from the list).
-template <typename R, bool SINGLE, int NPK, int NDK, int EV, int ENERGY, bool DENS = true>
+// te = [ns*ns][nbt][4] value cubics.
+template <typename R, bool SINGLE, int NPK, int NDK, int EV, int ENERGY>
 __device__ __forceinline__ void pair_terms(const PotArgs& P, const DevPotential& G, const R* tf, const R* te,
                                            int si, int sj, double r, R fpi, R fpj, R& g, R& phi)
 {
@@ -431,12 +430,10 @@ __device__ __forceinline__ void pair_terms(const PotArgs& P, const DevPotential&
             const R* c = tf + bin * FS;
             R dphi = quadratic(c, u);
             if (EV == EV_SPLIT) dphi = split_term<R, 2>(c + 6, u, dphi);
-            g = dphi;
-            if (DENS) {  // explicit fused forms: every kernel variant rounds alike
-                R drho = quadratic(c + 3, u);
-                if (EV == EV_SPLIT) drho = split_term<R, 2>(c + 8, u, drho);
-                g = fma(fpi + fpj, drho, dphi);
-            }
+            // explicit fused forms: every kernel variant rounds alike
+            R drho = quadratic(c + 3, u);
+            if (EV == EV_SPLIT) drho = split_term<R, 2>(c + 8, u, drho);
+            g = fma(fpi + fpj, drho, dphi);
             if (ENERGY == 1) {
                 const R* e = te + bin * VS;
                 phi = cubic(e, u);
@@ -447,16 +444,13 @@ __device__ __forceinline__ void pair_terms(const PotArgs& P, const DevPotential&
             const R* c = tf + (ab * P.nbt + bin) * FS;
             R dphi = quadratic(c, u);
             if (EV == EV_SPLIT) dphi = split_term<R, 2>(c + 6, u, dphi);
-            g = dphi;
-            if (DENS) {
-                const R* c2 = tf + (ba * P.nbt + bin) * FS;
-                R dab = quadratic(c + 3, u), dba = quadratic(c2 + 3, u);
-                if (EV == EV_SPLIT) {
-                    dab = split_term<R, 2>(c + 8, u, dab);
-                    dba = split_term<R, 2>(c2 + 8, u, dba);
-                }
-                g = fma(fpi, dab, fma(fpj, dba, dphi));
+            const R* c2 = tf + (ba * P.nbt + bin) * FS;
+            R dab = quadratic(c + 3, u), dba = quadratic(c2 + 3, u);
+            if (EV == EV_SPLIT) {
+                dab = split_term<R, 2>(c + 8, u, dab);
+                dba = split_term<R, 2>(c2 + 8, u, dba);
             }
+            g = fma(fpi, dab, fma(fpj, dba, dphi));
             if (ENERGY == 1) {
                 const R* e = te + (ab * P.nbt + bin) * VS;
                 phi = cubic(e, u);
@@ -468,7 +462,7 @@ __device__ __forceinline__ void pair_terms(const PotArgs& P, const DevPotential&
         R dphi;
         if (ENERGY == 1) knot_both<R, NPK>(C1.pa, C1.pd, C1.pr, r, phi, dphi);
         else dphi = knot_deriv<R, NPK>(C1.pd, C1.pr, r);
-        g = DENS ? fma(fpi + fpj, knot_deriv<R, NDK>(C1.dd, C1.dr, r), dphi) : dphi;
+        g = fma(fpi + fpj, knot_deriv<R, NDK>(C1.dd, C1.dr, r), dphi);
     } else {
         const int ab = si * G.ns + sj, ba = sj * G.ns + si;
         KnotSet<R, NPK> kp;
@@ -476,13 +470,10 @@ __device__ __forceinline__ void pair_terms(const PotArgs& P, const DevPotential&
         R dphi;
         if (ENERGY == 1) knot_both<R, NPK>(kp.a, kp.d, kp.r, r, phi, dphi);
         else dphi = knot_deriv<R, NPK>(kp.d, kp.r, r);
-        g = dphi;
-        if (DENS) {
-            KnotSet<R, NDK> kab, kba;
-            load_knots<R, NDK>(G.dens_a[ab], G.dens_d[ab], G.dens_r[ab], kab);
-            load_knots<R, NDK>(G.dens_a[ba], G.dens_d[ba], G.dens_r[ba], kba);
-            g = fma(fpi, knot_deriv<R, NDK>(kab.d, kab.r, r), fma(fpj, knot_deriv<R, NDK>(kba.d, kba.r, r), g));
-        }
+        KnotSet<R, NDK> kab, kba;
+        load_knots<R, NDK>(G.dens_a[ab], G.dens_d[ab], G.dens_r[ab], kab);
+        load_knots<R, NDK>(G.dens_a[ba], G.dens_d[ba], G.dens_r[ba], kba);
+        g = fma(fpi, knot_deriv<R, NDK>(kab.d, kab.r, r), fma(fpj, knot_deriv<R, NDK>(kba.d, kba.r, r), dphi));
     }
 }
 
