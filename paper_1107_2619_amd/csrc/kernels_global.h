@@ -89,6 +89,14 @@ __device__ __forceinline__ int4 record_load(__amdgpu_buffer_rsrc_t rs, int j)
 // NCH: neighbour records in flight per thread (2, 4 or 8; the autotuner picks
 // it): more hide more gather latency, fewer free registers for more waves.
 //
+// The compact mixed mode reads its list groups one round ahead (AHEAD), behind the
+// records of the round before, so that a round waits for one load and not for two
+// in a row; its registers allow it (58 of the 64 for eight waves).  Step times
+// without and with: 218,972 atoms 48.8 -> 47.5 us, 427,680 atoms 70.4 -> 69.9,
+// 1,013,760 atoms 160.0 -> 158.3, 48 two-species replicas of 8,100 atoms
+// 123.4 -> 121.0.  The FP64 mode loses (218,972 atoms 58.3 -> 60.6): it already
+// has twice the bytes in flight, and four registers more cost it a wave.
+//
 // TL: several species with all their tables staged in LDS, in workgroups of
 // kTableBlock threads that share one copy (one species always stages its own).
 
@@ -341,21 +349,31 @@ __global__ __launch_bounds__(TL ? kTableBlock : kBlock) void k_density(Buffers b
     constexpr int GR = NCH >= kChunk ? NCH / kChunk : 1;  // list groups per iteration
     constexpr int SUB = NCH >= kChunk ? 1 : kChunk / NCH;  // record batches per group
     static_assert(kChunk == 4 && NCH * SUB == kChunk * GR, "one int4 list load per four entries");
+    constexpr bool AHEAD = CMP != 0;  // list groups read one round ahead (groups past cap are padding)
+    int4 next[GR];
+    uint32_t tnext[GR];
+    if (AHEAD) {
+#pragma unroll
+        for (int g = 0; g < GR; ++g) {
+            next[g] = list_group(b, g, t, n_slots);
+            tnext[g] = type_group<SINGLE>(b, g, t, n_slots);
+        }
+    }
     for (int k0 = 0; k0 < n; k0 += kChunk * GR) {
         int v[kChunk * GR];
         uint32_t tv[GR];
         double sum[GR];
 #pragma unroll
-        for (int g = 0; g < GR; ++g) {  // groups past cap are padding
-            const int4 v4 = list_group(b, (k0 >> 2) + g, t, n_slots);
-            v[4 * g] = v4.x;
-            v[4 * g + 1] = v4.y;
-            v[4 * g + 2] = v4.z;
-            v[4 * g + 3] = v4.w;
+        for (int g = 0; g < GR; ++g) {
+            if (!AHEAD) next[g] = list_group(b, (k0 >> 2) + g, t, n_slots);
+            v[4 * g] = next[g].x;
+            v[4 * g + 1] = next[g].y;
+            v[4 * g + 2] = next[g].z;
+            v[4 * g + 3] = next[g].w;
         }
 #pragma unroll
         for (int g = 0; g < GR; ++g) {
-            tv[g] = type_group<SINGLE>(b, (k0 >> 2) + g, t, n_slots);
+            tv[g] = AHEAD ? tnext[g] : type_group<SINGLE>(b, (k0 >> 2) + g, t, n_slots);
             sum[g] = 0.0;
         }
 #pragma unroll
@@ -371,6 +389,13 @@ __global__ __launch_bounds__(TL ? kTableBlock : kBlock) void k_density(Buffers b
                 if (CMP) qs[u] = record_load(rs, e[u] & kIndexMask);
             }
             if (!CMP) S.template gather<STAGE, NCH>(pos, e, xs);
+            if (AHEAD && sb == 0 && k0 + kChunk * GR < n) {
+#pragma unroll
+                for (int g = 0; g < GR; ++g) {
+                    next[g] = list_group(b, (k0 >> 2) + GR + g, t, n_slots);
+                    tnext[g] = type_group<SINGLE>(b, (k0 >> 2) + GR + g, t, n_slots);
+                }
+            }
 #pragma unroll
             for (int u = 0; u < NCH; ++u) {
                 if (kb + u >= n) break;
@@ -611,20 +636,30 @@ __global__ __launch_bounds__(TL ? kTableBlock : kBlock, STAGE && EN == 0 && NCH 
     constexpr int GR = NCH >= kChunk ? NCH / kChunk : 1;  // list groups per iteration
     constexpr int SUB = NCH >= kChunk ? 1 : kChunk / NCH;  // record batches per group
     static_assert(kChunk == 4 && NCH * SUB == kChunk * GR, "one int4 list load per four entries");
+    constexpr bool AHEAD = CMP != 0;  // list groups read one round ahead (groups past cap are padding)
+    int4 next[GR];
+    uint32_t tnext[GR];
+    if (AHEAD) {
+#pragma unroll
+        for (int g = 0; g < GR; ++g) {
+            next[g] = list_group(b, g, t, n_slots);
+            tnext[g] = type_group<SINGLE>(b, g, t, n_slots);
+        }
+    }
     for (int k0 = 0; k0 < n; k0 += kChunk * GR) {
         int v[kChunk * GR];
         uint32_t tv[GR];
         PairAcc sum[GR];
 #pragma unroll
-        for (int g = 0; g < GR; ++g) {  // groups past cap are padding
-            const int4 v4 = list_group(b, (k0 >> 2) + g, t, n_slots);
-            v[4 * g] = v4.x;
-            v[4 * g + 1] = v4.y;
-            v[4 * g + 2] = v4.z;
-            v[4 * g + 3] = v4.w;
+        for (int g = 0; g < GR; ++g) {
+            if (!AHEAD) next[g] = list_group(b, (k0 >> 2) + g, t, n_slots);
+            v[4 * g] = next[g].x;
+            v[4 * g + 1] = next[g].y;
+            v[4 * g + 2] = next[g].z;
+            v[4 * g + 3] = next[g].w;
         }
 #pragma unroll
-        for (int g = 0; g < GR; ++g) tv[g] = type_group<SINGLE>(b, (k0 >> 2) + g, t, n_slots);
+        for (int g = 0; g < GR; ++g) tv[g] = AHEAD ? tnext[g] : type_group<SINGLE>(b, (k0 >> 2) + g, t, n_slots);
 #pragma unroll
         for (int sb = 0; sb < SUB; ++sb) {
             const int kb = k0 + sb * NCH;
@@ -638,6 +673,13 @@ __global__ __launch_bounds__(TL ? kTableBlock : kBlock, STAGE && EN == 0 && NCH 
                 if (CMP) qs[u] = record_load(rs, e[u] & kIndexMask);
             }
             if (!CMP) S.template gather<STAGE, NCH>(pos, e, ps);
+            if (AHEAD && sb == 0 && k0 + kChunk * GR < n) {
+#pragma unroll
+                for (int g = 0; g < GR; ++g) {
+                    next[g] = list_group(b, (k0 >> 2) + GR + g, t, n_slots);
+                    tnext[g] = type_group<SINGLE>(b, (k0 >> 2) + GR + g, t, n_slots);
+                }
+            }
 #pragma unroll
             for (int u = 0; u < NCH; ++u) {
                 if (kb + u >= n) break;
