@@ -1625,14 +1625,17 @@ int md_energy(md_ctx* c, md_energies* out, void* stream)
     std::vector<double> pr((size_t)c->R * nps, 0.0);
     int32_t flags[F_COUNT] = {};
     // flags, energies, thermostat and barostat states lie one behind the other in
-    // the workspace: one copy, which also waits for the stream (each takes ~10 us)
+    // the workspace: one copy (each takes ~10 us) on the null stream, which waits
+    // for its own work and that of every blocking stream; another stream is waited
+    // for first (refused while it captures)
     const char* from = reinterpret_cast<const char*>(c->buf.flags);
     auto at = [&](const void* p) { return (size_t)(static_cast<const char*>(p) - from); };
     const size_t bytes = c->pr     ? at(c->buf.pr_state) + pr.size() * 8
                          : c->nvt  ? at(c->buf.nh_state) + nh.size() * 8
                                    : at(c->buf.energies) + e.size() * 8;
     std::vector<char> got(bytes);
-    if (!hip_ok(c, hipMemcpyWithStream(got.data(), from, bytes, hipMemcpyDeviceToHost, s), "md_energy copy"))
+    if ((s && !hip_ok(c, hipStreamSynchronize(s), "md_energy sync")) ||
+        !hip_ok(c, hipMemcpy(got.data(), from, bytes, hipMemcpyDeviceToHost), "md_energy copy"))
         return MD_ERR_DEVICE;
     collect_times(c);
     std::memcpy(flags, got.data(), sizeof flags);
