@@ -1693,19 +1693,21 @@ int md_energy_history(md_ctx* c, md_energies* out, int64_t max_entries, int64_t*
     c->ring_read = std::max(c->ring_read, pushed - c->ring_len);
     const int64_t n = std::min(pushed - c->ring_read, max_entries);
     const size_t per = (size_t)c->R * kEnergySlots;
-    std::vector<double> v(per * (size_t)std::max<int64_t>(n, 0));
-    for (int64_t j = 0; j < n;) {  // the ring's entries in at most two pieces
-        const int64_t i = (c->ring_read + j) % c->ring_len, k = std::min(n - j, c->ring_len - i);
-        if (!hip_ok(c, hipMemcpy(v.data() + (size_t)j * per, c->buf.ering + (size_t)i * per, (size_t)k * per * 8,
-                                 hipMemcpyDeviceToHost), "md_energy_history copy"))
-            return MD_ERR_DEVICE;
-        j += k;
-    }
+    // the ring's entries in pieces that end with the ring or fill 1 MiB of host
+    // memory (one entry at least)
+    const int64_t piece = std::max<int64_t>(1, ((int64_t)1 << 20) / (int64_t)(per * 8));
+    std::vector<double> v(per * (size_t)std::max<int64_t>(std::min(n, piece), 0));
     const std::vector<double> none;
-    for (int64_t j = 0; j < n; ++j)
-        for (int r = 0; r < c->R; ++r)
-            fill_energies(c, r, v.data() + (size_t)j * per + (size_t)r * kEnergySlots, none, none,
-                          c->ring_steps[c->ring_read + j], out[j * c->R + r]);
+    for (int64_t j = 0; j < n;) {
+        const int64_t i = (c->ring_read + j) % c->ring_len, k = std::min({n - j, c->ring_len - i, piece});
+        if (!hip_ok(c, hipMemcpy(v.data(), c->buf.ering + (size_t)i * per, (size_t)k * per * 8, hipMemcpyDeviceToHost),
+                    "md_energy_history copy"))
+            return MD_ERR_DEVICE;
+        for (int64_t e = 0; e < k; ++e, ++j)
+            for (int r = 0; r < c->R; ++r)
+                fill_energies(c, r, v.data() + (size_t)e * per + (size_t)r * kEnergySlots, none, none,
+                              c->ring_steps[c->ring_read + j], out[j * c->R + r]);
+    }
     c->ring_read += n;
     *n_out = n;
     return MD_OK;
