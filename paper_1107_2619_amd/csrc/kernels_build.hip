@@ -714,7 +714,7 @@ __device__ __forceinline__ void list_cell(const Buffers& b, int p, int q, int64_
     // the candidates that remain for a chunk of own atoms, as table indices
     __shared__ uint16_t kept_table[kBlock / kWave][kCandTable];
     uint16_t* kept = kept_table[threadIdx.x / kWave];
-    const float prune = sqrtf((float)rlist2) + 1e-3f;
+    const float rlist = sqrtf((float)rlist2), prune = rlist + (1e-3f + 1e-6f * rlist);
     const float prune2 = prune * prune;
 
     const double4* __restrict__ pos = b.pos[p];
@@ -735,8 +735,9 @@ __device__ __forceinline__ void list_cell(const Buffers& b, int p, int q, int64_
                       tabled, false, any_wrap, excl, nb_start, nb_wrap, nb_code};
         // Candidates beyond the list radius of the box around these atoms are
         // left out first (in FP32 relative to the first own atom, with a margin
-        // of 0.001 A: rounding below 1000 A is 6e-5 A; not where pairs take their
-        // minimum image one by one).  The tests, ~20 vector instructions per own
+        // of 0.001 A + 1e-6 of the radius: where the box is below 1000 A wide, the
+        // candidates near the limit are rounded by 6e-5 A + 6e-8 of the radius per
+        // step; not where pairs take their minimum image one by one).  The tests, ~20 vector instructions per own
         // atom and 64 candidates, bound this kernel, and about half of the 27
         // cells' candidates go.  It pays from ~10 atoms per cell: Fe-C replicas
         // at a 0.8 A skin 211 -> 157 us per build with the gather, the fcc slab
