@@ -598,7 +598,9 @@ __device__ __forceinline__ void test_candidates(const ListOut& L, const ListWork
 // rows; a lane without a source keeps its value.  Written as one block of DPP
 // minima, one instruction per step and value (the builtins take four: a move,
 // two quieting maxima, the minimum); a value is read five instructions after it
-// was written, beyond the two wait states DPP asks for.
+// was written, beyond the two wait states DPP asks for.  The compiler does not see
+// into a block, so each also waits at its ends: two states before its first DPP
+// read, one after its last write, which a lane read may follow at once.
 __device__ __forceinline__ void wave_min(float (&v)[6], int n)
 {
 #define MDK_DPP_STEP(ctrl)                      \
@@ -613,12 +615,14 @@ __device__ __forceinline__ void wave_min(float (&v)[6], int n)
                  MDK_DPP_STEP("row_shr:2 row_mask:0xf bank_mask:0xf")
                  MDK_DPP_STEP("row_shr:4 row_mask:0xf bank_mask:0xf")
                  MDK_DPP_STEP("row_shr:8 row_mask:0xf bank_mask:0xf")
+                 "s_nop 0"
                  : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]));
     int last = 15;  // lane 15 of a row holds its minimum
     if (n > 16) {
         asm volatile("s_nop 1\n\t"
                      MDK_DPP_STEP("row_bcast:15 row_mask:0xa bank_mask:0xf")
                      MDK_DPP_STEP("row_bcast:31 row_mask:0xc bank_mask:0xf")
+                     "s_nop 0"
                      : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]));
         last = kWave - 1;
     }
