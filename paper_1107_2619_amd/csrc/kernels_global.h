@@ -418,14 +418,28 @@ __global__ __launch_bounds__(TL ? kTableBlock : kBlock) void k_density(Buffers b
 // What bounds a small system is the chain of dependent loads of one thread
 // (list, records, list, ...: seven times ~2 us for 28 neighbours), on a chip it
 // does not fill: at 2000 atoms 32 wavefronts for 1024 SIMDs.  Dealing the seven
-// groups to eight waves leaves one link of that chain.  Step times, one thread
-// per atom against split (FP64; mixed): 2000 atoms 39.5 -> 17.2 us
-// (28.3 -> 15.7), 31,250 atoms 39.8 -> 21.1 (29.5 -> 19.3), 93,312 atoms
-// 47.6 -> 37.8 (37.7 -> 30.6), 146,694 atoms 56.6 -> 51.6 (46.7 -> 40.6),
-// 247,500 atoms 66.8 -> 77.4 (56.8 -> 58.9); two species 16,000 atoms
-// 66.5 -> 23.1 (51.1 -> 20.2), 148,176 atoms 79.9 -> 89.8 (64.7 -> 64.4).
-// Beyond two one-thread wavefronts per SIMD the chip is full without it and the
-// repeated prologues and table copies cost more (KernelShape::split).
+// groups to eight waves leaves one link of that chain.  As the chip fills, the
+// repeated prologues, table copies and exchanges of the sums through LDS cost
+// more than that (KernelShape::split, split_sums).  Step times in us, one thread
+// per atom against split in every pass, by slots (1.0 = 65,536, one one-thread
+// wavefront per SIMD):
+//   plain steps       one species FP64     mixed            two species FP64  mixed
+//     1,984 (0.03)    34.7 -> 17.5     24.6 -> 15.9     50.0 -> 17.6     37.7 -> 16.4
+//    64,896 (0.99)    37.5 -> 30.7     28.1 -> 24.5     53.1 -> 34.9     42.0 -> 26.4
+//   100,352 (1.53)    42.2 -> 39.4     33.3 -> 32.3     56.4 -> 48.8     45.0 -> 36.2
+//   126,720 (1.93)    45.9    45.7     35.8    36.2     59.1 -> 56.9     47.2 -> 41.5
+//   168,704 (2.57)    52.0 <- 56.9     41.2 <- 44.0     60.3 <- 70.8     48.5 <- 50.6
+//   energies every step
+//    77,824 (1.19)    56.8 -> 55.0     48.7 -> 47.9     74.4 -> 61.0     63.8 -> 49.8
+//    84,928 (1.30)    59.0    59.3     49.5 <- 50.9     74.5 -> 64.7     63.9 -> 52.0
+//   108,672 (1.66)    59.0 <- 66.3     51.1 <- 56.3     76.1 -> 73.8     65.1 -> 58.0
+//   126,720 (1.93)    62.8 <- 73.3     53.7 <- 62.2     78.6 <- 81.2     67.1 -> 64.1
+//   168,704 (2.57)    70.7 <- 89.7     60.3 <- 75.3     79.9 <- 100      68.7 <- 76.3
+// Barostat steps (virial) cross at 1.4 (FP64) and 1.3 with one species, 1.7 and 2.0
+// with two; rows of 40 to 160 entries cross where those of 28 do.  The sums of a
+// group are ten values instead of three: the force pass with sums goes back to one
+// thread per atom earlier, the density pass beside it does not (126,720 atoms FP64
+// with energies: force one thread, density either form 63 us).
 //
 // Four waves instead of eight: 22.1 us at 16,000 atoms (eight 18.7), 49.2 at
 // 146,694 (51.6).
@@ -1064,7 +1078,7 @@ static void force_tables(const Buffers& b, int p, int q, const KernelShape& k, c
     const size_t split_lds =
         S && EV != EV_KNOTS ? (size_t)P.nbt * (force_stride(EV) + (E == 1 || E == 4 ? value_stride(EV) : 0)) * sizeof(R)
                             : 0;
-    if (k.split && split_lds + split_partials(force_sums(E)) <= kSplitLds) {
+    if ((E == 0 ? k.split : k.split_sums) && split_lds + split_partials(force_sums(E)) <= kSplitLds) {
         hipLaunchKernelGGL((k_force_split<R, S, NP, ND, EV, E, C, O, W, CMP>), dim3((unsigned)(k.n_slots / kWave)),
                            dim3(kWave * kSplit), split_lds, s, b, p, q, k.n_slots, k.cap, P, dt_fs, st);
         return;

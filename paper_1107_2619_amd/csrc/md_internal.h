@@ -253,7 +253,8 @@ struct KernelShape {
     int32_t pairs;     // LDS bricks with each pair of two own atoms once (MD_OPT_KERNEL = 2)
     int32_t nchunk;    // neighbour records in flight per thread in the global kernels: 2, 4 or 8
     int32_t list_types; // the global list also stores its entries' type bytes (several species)
-    int32_t split;     // 1 = the global kernels deal each atom's neighbours to kSplit waves
+    int32_t split;     // 1 = the density pass and the plain force pass deal each atom's neighbours to kSplit waves
+    int32_t split_sums;  // 1 = so does the force pass that also sums energies or the virial
     int32_t stage;     // 1 = the FP64 one-thread kernels stage their own slots' records in LDS
     int32_t chunked;  // 1 = per-replica sums of the thermostat and barostat start with
                       // per-chunk sums (some replica spans more than kChunkedSumWaves waves)

@@ -205,8 +205,11 @@ KernelShape shape(const md_ctx* c)
     k.chunked = c->chunked_sums ? 1 : 0;
     k.lds_limit = c->lds_limit;
     k.nchunk = c->nchunk;
-    // few atoms: up to two one-thread wavefronts per SIMD (see kernels_global.h)
-    k.split = c->Np <= (int64_t)2 * kSimds * kWave;
+    // few atoms: up to two one-thread wavefronts per SIMD; fewer with sums, earlier for
+    // one species, whose one-thread passes are the shorter (see kernels_global.h)
+    constexpr int64_t per_simd = (int64_t)kSimds * kWave;  // slots of one wavefront per SIMD
+    k.split = c->Np <= 2 * per_simd;
+    k.split_sums = 4 * c->Np <= (c->single ? 5 : c->precision == MD_FP64 ? 7 : 8) * per_simd;
     // many atoms: beyond four wavefronts per SIMD the gathers bind, not their latency
     k.stage = c->Np > (int64_t)4 * kSimds * kWave;
     k.list_types = c->single ? 0 : 1;
