@@ -107,3 +107,67 @@ def test_passes_with_sums(md, precision, potential, waves, mode):
     announce(f"passes with sums, {mode} {precision} {potential} at {waves}")
     parts, fill = _parts(5, (250, 127, 64, 65, 1), potential, 0.3, 64)
     _both_sides(md, parts, fill, int(waves * PER_SIMD), mode=mode, precision=precision)
+
+
+@pytest.mark.parametrize("mode", ["nvt", "npt", "full_npt", "gear"])
+@pytest.mark.parametrize("precision,potential,waves", [
+    ("fp64", "fe_fs", 2), ("mixed", "fe_fs", 2), ("fp64", "fec_eam", 2), ("fp64", "fe_fs", 4), ("mixed", "fe_fs", 4)])
+def test_integrators(md, precision, potential, waves, mode):
+    """The sums a force pass takes per wavefront for the thermostat and the barostats
+    (whose padding lanes stay to the end), and the Gear steps, in every form."""
+    announce(f"{mode} {precision} {potential} at {waves}")
+    parts, fill = _parts(5, (250, 127, 64, 65, 1), potential, 0.3, 64)
+    _both_sides(md, parts, fill, waves * PER_SIMD, mode=mode, precision=precision)
+
+
+@pytest.mark.parametrize("waves", [2, 4])
+def test_knot_sums(md, waves):
+    """The term-by-term evaluator, which needs no tables beside the staged records."""
+    announce(f"knot sums at {waves}")
+    parts, fill = _parts(5, (250, 127, 64, 65, 1), "fe_fs", 0.3, 64)
+    _both_sides(md, parts, fill, waves * PER_SIMD, evaluator=1)
+
+
+@pytest.mark.parametrize("precision,potential,waves", [
+    ("fp64", "fe_fs", 2), ("mixed", "fe_fs", 2), ("fp64", "fec_eam", 2), ("mixed", "fec_eam", 2), ("fp64", "fe_fs", 4)])
+def test_neighbour_chunk_beyond_the_split_form(md, precision, potential, waves):
+    """Two, four or eight neighbour records in flight where they take effect: one
+    thread per atom, from the caches and staged, with energies on every second step;
+    rows whose lengths leave every remainder of a chunk."""
+    announce(f"neighbour chunk {precision} {potential} at {waves}")
+    parts, fill = _parts(5, (250, 127, 64, 65, 1), potential, 0.3, 64)
+    s = _filled(parts, fill, int(waves * PER_SIMD) + 64)
+    n = sum(p.n_atoms for p in parts)
+    counts = md.Simulation(s, precision=precision)
+    counts.build_neighbours()
+    assert set(counts.neighbours()[0][:n] % 8) == set(range(8))
+    runs = [_run(md, s, n, len(parts), precision=precision, chunk=c) for c in (4, 2, 8)]
+    for other in runs[1:]:
+        for a, b in zip(runs[0], other):
+            assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("potential,skin,cap,rounds,inner_rounds", [
+    ("fe_fs", 1.6, 90, 2, 2), ("fe_fs", 2.8, 133, 4, 4), ("fec_eam", 2.0, 101, 3, 2)])
+def test_rounds_of_the_split_form(md, orc, precision, potential, skin, cap, rounds, inner_rounds):
+    """Rows of two to four rounds of eight groups of four, the inner entries (the
+    density pass) of two or four: forces and per-atom energies against the oracle."""
+    announce(f"split rounds {precision} {potential} skin {skin}")
+    s = _take(inputs.bcc_fe(6, seed=95, displace=0.06, skin=skin, potential=potential), 431)
+    s.max_neighbours = cap
+    if potential == "fec_eam":
+        s.species[::5] = 1
+    d = s.pos[:, None] - s.pos[None]
+    d -= s.box[0] * np.rint(d / s.box[0])
+    r = np.sqrt(np.sum(d * d, 2)) + 1e9 * np.eye(s.n_atoms)
+    inner = np.max(np.sum(r < float(np.max(s.potential["dens_R"])) + skin, 1))
+    ref = orc.forces(s.pos, s.species, s.box[0], s.periodic[0], orc.Potential(s.potential))
+    sim = md.Simulation(s, precision=precision)
+    sim.eam_forces()
+    en = sim.energy()
+    longest = sim.get_option(md.MD_OPT_MAX_COUNT)
+    assert longest <= cap and (longest + 31) // 32 == rounds and (inner + 31) // 32 == inner_rounds
+    assert force_error(sim.forces(), ref.f) <= TOL[precision]["force"]
+    assert energy_error(sim.atom_energies(), ref.e_atom) <= TOL[precision]["energy"]
+    assert abs(en.pe[0] - ref.pe) <= TOL[precision]["energy"] * abs(ref.pe)
