@@ -356,10 +356,13 @@ enum {
                                   grows by entries * R * 96 bytes); set before
                                   md_workspace_bytes and md_bind (MD_ERR_STATE
                                   after md_bind).  Default 0: no ring                */
-    MD_OPT_NEIGHBOUR_CHUNK = 17, /* global kernels: neighbour records each thread
-                                  gathers before it evaluates them, 2, 4 (default)
-                                  or 8; md_autotune picks it.  Results do not
-                                  depend on it (same terms, same order)              */
+    MD_OPT_NEIGHBOUR_CHUNK = 17, /* global kernels with one thread per atom (systems
+                                  beyond 131,072 slots, sooner on energy steps; the
+                                  passes of smaller ones have no such choice):
+                                  neighbour records each thread gathers before it
+                                  evaluates them, 2, 4 (default) or 8; md_autotune
+                                  picks it.  Results do not depend on it (same
+                                  terms, same order)                                 */
     MD_OPT_AUTO_REBUILD = 18   /* 1 = rebuild on displacement instead of every
                                   rebuild_every steps ("The Neighbourlist
                                   calculation": the list of r_c + skin stays

@@ -444,13 +444,6 @@ __global__ __launch_bounds__(TL ? kTableBlock : kBlock) void k_density(Buffers b
 // Four waves instead of eight: 22.1 us at 16,000 atoms (eight 18.7), 49.2 at
 // 146,694 (51.6).
 
-// Sums per atom of the force pass in energy mode E.
-constexpr int force_sums(int E) { return E == 0 ? 3 : E == 1 || E == 4 ? 10 : E == 2 ? 6 : 9; }
-constexpr size_t split_partials(int sums) { return sizeof(double) * kWave * (kSplit - 1) * sums; }
-// LDS one split workgroup may take (tables and partial sums): two fit on a CU;
-// larger tables stay with the one-thread form, which shares a copy of them
-// among more atoms.
-constexpr size_t kSplitLds = 64 * 1024;
 
 template <typename R, bool SINGLE, int NPK, int NDK, int EV, int CMP>
 __global__ __launch_bounds__(kWave * kSplit) void k_density_split(Buffers b, int p, int q, int64_t n_slots, int cap,
@@ -979,7 +972,7 @@ static void density_tables(const Buffers& b, int p, int q, const KernelShape& k,
                            hipStream_t s)
 {
     const size_t split_lds = S && EV != EV_KNOTS ? (size_t)P.nbt * value_stride(EV) * sizeof(R) : 0;
-    if (k.split && split_lds + split_partials(1) <= kSplitLds) {
+    if (k.split && split_fits(split_lds, 1)) {
         hipLaunchKernelGGL((k_density_split<R, S, NP, ND, EV, CMP>), dim3((unsigned)(k.n_slots / kWave)),
                            dim3(kWave * kSplit), split_lds, s, b, p, q, k.n_slots, k.cap, P, energy);
         return;
@@ -1078,7 +1071,7 @@ static void force_tables(const Buffers& b, int p, int q, const KernelShape& k, c
     const size_t split_lds =
         S && EV != EV_KNOTS ? (size_t)P.nbt * (force_stride(EV) + (E == 1 || E == 4 ? value_stride(EV) : 0)) * sizeof(R)
                             : 0;
-    if ((E == 0 ? k.split : k.split_sums) && split_lds + split_partials(force_sums(E)) <= kSplitLds) {
+    if ((E == 0 ? k.split : k.split_sums) && split_fits(split_lds, force_sums(E))) {
         hipLaunchKernelGGL((k_force_split<R, S, NP, ND, EV, E, C, O, W, CMP>), dim3((unsigned)(k.n_slots / kWave)),
                            dim3(kWave * kSplit), split_lds, s, b, p, q, k.n_slots, k.cap, P, dt_fs, st);
         return;

@@ -66,6 +66,15 @@ constexpr int kValueStrideSplit = 6;
 // table kind: 0 = term-by-term knot sums, 1 = knots on the bin grid, 2 = knots inside bins
 constexpr int force_stride(int kind) { return kind == 2 ? kForceStrideSplit : kForceStride; }
 constexpr int value_stride(int kind) { return kind == 2 ? kValueStrideSplit : kValueStride; }
+// Sums per atom of the force pass in energy mode E.
+constexpr int force_sums(int E) { return E == 0 ? 3 : E == 1 || E == 4 ? 10 : E == 2 ? 6 : 9; }
+// Whether a split workgroup's tables and partial sums leave room for a second one
+// on its CU; larger tables stay with the one-thread form, which shares a copy of
+// them among more atoms.
+constexpr bool split_fits(size_t table_bytes, int sums)
+{
+    return table_bytes + sizeof(double) * kWave * (kSplit - 1) * sums <= 64 * 1024;
+}
 // Compact gather record of the mixed mode: cell-local coordinates as 32-bit
 // fixed point in units of h_a 2^-kCompactBits (h_a the link-cell edge of axis
 // a) and F' as FP32, 16 bytes.  A coordinate may lie up to kCompactCells cell

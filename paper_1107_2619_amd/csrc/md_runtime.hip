@@ -1955,7 +1955,13 @@ int md_autotune(md_ctx* c, int32_t trials, void* stream)
     if (c->precision == MD_FP64 && c->table_ok && c->explicit_ok) evals = {0, 1};
     std::vector<Cand> cands;
     for (int32_t e : evals) {
-        for (int32_t nch : {4, 2, 8}) cands.push_back({1, 0, 0, 512, e, nch});
+        // (the split form of small systems has no chunk to choose)
+        const int kind = e == 0 ? c->table_kind : 0;
+        const size_t bin = kind && c->single ? (size_t)c->args.nbt * (c->precision == MD_FP64 ? 8 : 4) : 0;
+        const bool split = shape(c).split && split_fits(bin * value_stride(kind), 1) &&
+                           split_fits(bin * force_stride(kind), force_sums(0));
+        for (int32_t nch : {4, 2, 8})
+            if (nch == 4 || !split) cands.push_back({1, 0, 0, 512, e, nch});
         // the brick kernels take fixed orthorhombic boxes and scheduled builds
         if (c->nbr_mode == MD_NBR_FULL && !c->pr && !c->tri && !c->auto_rebuild)
             // (the pair kernels, MD_OPT_KERNEL = 2, are left out: their LDS
