@@ -114,6 +114,14 @@ __device__ __forceinline__ int4 record_load(__amdgpu_buffer_rsrc_t rs, int j)
 // as well at 1,013,760 atoms (165.5 us) and worse at 427,680 (99, the last round
 // of workgroups).
 //
+// Beside large tables the staged records would cost more than they save: they are
+// staged where the LDS of a CU still holds four workgroups of the force pass, or six
+// of the density pass, whose registers allow more (kStageLds).  Steps of 1,013,760
+// atoms, from the caches and staged, by the LDS of the staged force pass: 18 KB 185 ->
+// 164 us, 24 KB 191 -> 175, 28 KB 191 -> 173, 34 KB (energies) 234 -> 230; 40.2 KB 195
+// and 207, 41.2 KB (energies) 230 and 243, 59 KB (energies) 258 and 297; density
+// alone: 26 KB 195 -> 191, 32 KB 214 and 218.
+//
 // The two halves of a record lie in separate arrays, so that a random 16-byte read
 // may fall on any bank.  FULL: with F' (the force pass).
 //
@@ -121,6 +129,9 @@ __device__ __forceinline__ int4 record_load(__amdgpu_buffer_rsrc_t rs, int j)
 // plain ones the compiler may merge a lane's LDS and global read into one flat
 // load, which costs the whole gain.
 typedef double double2v __attribute__((ext_vector_type(2)));
+
+template <bool FULL>
+constexpr size_t kStageLds = 160 * 1024 / (FULL ? 4 : 6);
 
 template <bool FULL>
 struct Stage {
@@ -986,7 +997,7 @@ static void density_tables(const Buffers& b, int p, int q, const KernelShape& k,
         }
     }
     if constexpr (S && sizeof(R) == 8) {
-        if (k.stage && bytes + Stage<false>::kBytes <= (size_t)k.lds_limit) {
+        if (k.stage && bytes + Stage<false>::kBytes <= kStageLds<false>) {
             density_chunked<R, S, NP, ND, EV, CMP, false, true>(b, p, q, k, P, energy, bytes + Stage<false>::kBytes, s);
             return;
         }
@@ -1088,7 +1099,7 @@ static void force_tables(const Buffers& b, int p, int q, const KernelShape& k, c
         }
     }
     if constexpr (S && sizeof(R) == 8) {
-        if (k.stage && bytes + Stage<true>::kBytes <= (size_t)k.lds_limit) {
+        if (k.stage && bytes + Stage<true>::kBytes <= kStageLds<true>) {
             force_chunked<R, S, NP, ND, EV, E, C, O, W, CMP, false, true>(b, p, q, k, P, dt_fs, st,
                                                                          bytes + Stage<true>::kBytes, s);
             return;

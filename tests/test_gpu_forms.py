@@ -171,3 +171,18 @@ def test_rounds_of_the_split_form(md, orc, precision, potential, skin, cap, roun
     assert force_error(sim.forces(), ref.f) <= TOL[precision]["force"]
     assert energy_error(sim.atom_energies(), ref.e_atom) <= TOL[precision]["energy"]
     assert abs(en.pe[0] - ref.pe) <= TOL[precision]["energy"] * abs(ref.pe)
+
+
+@pytest.mark.parametrize("knots", [{1: 2.59}, {0: 2.2071, 1: 2.2171}, {1: 2.585}])
+def test_staging_beside_larger_tables(md, knots):
+    """Tables of 412 and 822 bins, with and without knots inside bins: beside them
+    the records of the density pass, the force pass, both or neither are staged."""
+    announce(f"staging with knots {knots}")
+    parts, fill = _parts(5, (250, 127, 64, 65, 1), "fe_fs", 0.3, 64)
+    pot = dict(fill.potential, pair_r=np.array(fill.potential["pair_r"]))
+    for k, r in knots.items():
+        pot["pair_r"][..., k] = r
+    for p in (*parts, fill):
+        p.potential = pot
+    for mode in ("nve", "nvt"):
+        _both_sides(md, parts, fill, 4 * PER_SIMD, mode=mode)
