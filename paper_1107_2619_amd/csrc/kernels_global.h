@@ -598,13 +598,22 @@ __device__ __forceinline__ void force_epilogue(const Buffers& b, int p, int q, i
     }
 }
 
+// Wavefronts per SIMD the staged plain pass is held to.  (Not where it closes a
+// thermostat step on tables with knots inside bins: held to six it spills, and a step
+// of 1,013,760 atoms takes 252 us, 219 with the registers it asks for.)
+template <int EV, int EN, bool CLOSE, bool OPEN, bool WRITEBACK, int NCH, bool STAGE>
+constexpr int kForceWaves = STAGE && EN == 0 && NCH <= 4 &&
+                                    !(EV == EV_SPLIT && boundary_sums<EN, CLOSE, OPEN, WRITEBACK>())
+                                ? 6
+                                : 1;
+
 // Force pass + velocity Verlet, one thread per atom.
 //
 // EN = 4: the energies and virial of energy mode 1, summed per wavefront in the
 // kernel (the reduction then reads one record per 64 atoms).
 template <typename R, bool SINGLE, int NPK, int NDK, int EV, int EN, bool CLOSE, bool OPEN, bool WRITEBACK,
           int CMP, int NCH, bool TL, bool STAGE>
-__global__ __launch_bounds__(TL ? kTableBlock : kBlock, STAGE && EN == 0 && NCH <= 4 ? 6 : 1) void k_force(
+__global__ __launch_bounds__(TL ? kTableBlock : kBlock, (kForceWaves<EV, EN, CLOSE, OPEN, WRITEBACK, NCH, STAGE>)) void k_force(
     Buffers b, int p, int q, int64_t n_slots, PotArgs P, double dt, md_state st)
 {
     constexpr bool WSUM = EN == 4;
