@@ -150,7 +150,7 @@ __device__ __forceinline__ int32_t block_sum(int32_t v)
     return all;
 }
 
-// Population of cell i in this build.
+// Whether cell i belongs to a replica that keeps its list in this build.
 __device__ __forceinline__ bool cell_kept(const Buffers& b, int64_t i, const int32_t* gate)
 {
     if (!gate) return false;
@@ -745,8 +745,12 @@ __device__ __forceinline__ void list_cell(const Buffers& b, int p, int q, int64_
         // atom and 64 candidates, bound this kernel, and about half of the 27
         // cells' candidates go.  It pays from ~10 atoms per cell: Fe-C replicas
         // at a 0.8 A skin 211 -> 157 us per build with the gather, the fcc slab
-        // 120 -> 95, sheared 128,000 atoms 81 -> 60; at 7 atoms per cell the
-        // leaving out costs what it saves (1,013,760 atoms FP64 291 -> 305).
+        // 120 -> 95, sheared 128,000 atoms 81 -> 60.  At 7 atoms per cell it costs about
+        // what it saves (without it every build is 1 to 4% slower still), and the order
+        // of the rows comes on top: whole builds against those of unordered rows, 1,013,760
+        // atoms FP64 363 -> 364 us and mixed 377 -> 395, 2,635,380 atoms 942 -> 970 and 959
+        // -> 1009.  A step that uses the list has it back in its density pass (mixed 56 ->
+        // 42); with a build at every step mixed loses 1.5% at the former size (486 -> 494).
         if (tabled && amb == 0) {
             const double xr = bcast_lane(xl.x, 0), yr = bcast_lane(xl.y, 0), zr = bcast_lane(xl.z, 0);
             const float ox = (float)(xl.x - xr), oy = (float)(xl.y - yr), oz = (float)(xl.z - zr);
@@ -867,12 +871,11 @@ __global__ __launch_bounds__(kBlock, TRI ? 4 : LOOP ? 5 : 6) void k_cell_list(Bu
 
 }  // namespace
 
-void launch_rebuild(const Buffers& b, int p, int q, const KernelShape& k, double half_skin2,
-                    int half_list, const int32_t* gate, hipStream_t s)
+void launch_rebuild(const Buffers& b, int p, int q, const KernelShape& k, double half_skin2, const int32_t* gate,
+                    hipStream_t s)
 {
     // p, q: current buffers; the sorted state lands in p^1, q^1.  The cell
     // populations are binned into bin_count, which every build leaves zeroed.
-    (void)half_list;
     const int64_t slot_blocks = gate ? std::min<int64_t>(blocks_for(k.n_slots), kGatedBlocks) : blocks_for(k.n_slots);
     hipLaunchKernelGGL(k_bin, dim3(slot_blocks), dim3(kBlock), 0, s, b, p, q, k.n_slots,
                        half_skin2, half_skin2 >= 0.0 ? 1 : 0, gate);

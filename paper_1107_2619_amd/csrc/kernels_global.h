@@ -1067,7 +1067,7 @@ static void force_chunked(const Buffers& b, int p, int q, const KernelShape& k, 
 {
     const int block = TL ? kTableBlock : kBlock;
     const dim3 grid((unsigned)((k.n_slots + block - 1) / block));
-    constexpr bool step = ((E == 0 || E == 1 || E == 4) && C && O && !W) || (E == 0 && !C && !O && !W);
+    constexpr bool step = ((E == 0 || E == 4) && C && O && !W) || (E == 0 && !C && !O && !W);
     if constexpr (step) {
         if (k.nchunk == 2) {
             hipLaunchKernelGGL((k_force<R, S, NP, ND, EV, E, C, O, W, CMP, 2, TL, STAGE>), grid, dim3(block), lds, s, b,
@@ -1144,10 +1144,8 @@ static void force_variant(const Buffers& b, int p, int q, const KernelShape& k, 
     } else if (!fl.close && fl.open) {
         force_launch<R, S, NP, ND, EV, false, false, true, false>(b, p, q, k, P, dt_fs, st, s);
     } else if (fl.close && fl.open) {
-        if (fl.energy == 4)  // per-step energies, summed per wavefront
+        if (fl.energy)  // per-step energies, summed per wavefront (mode 4; no other comes here)
             force_launch<R, S, NP, ND, EV, 4, true, true, false>(b, p, q, k, P, dt_fs, st, s);
-        else if (fl.energy)  // per-step energies
-            force_launch<R, S, NP, ND, EV, true, true, true, false>(b, p, q, k, P, dt_fs, st, s);
         else force_launch<R, S, NP, ND, EV, false, true, true, false>(b, p, q, k, P, dt_fs, st, s);
     } else if (!fl.writeback && fl.energy == 3) {  // full-matrix barostat: closing kick, virial tensor
         force_launch<R, S, NP, ND, EV, 3, true, false, false>(b, p, q, k, P, dt_fs, st, s);

@@ -278,8 +278,8 @@ void launch_load_state(const Buffers& b, int p, int q, const md_state& st, const
 // gate: NULL rebuilds every replica; otherwise only the replicas whose entry
 // gate[1 + r] is set (automatic rebuilds; every kernel exits at once for the
 // others).
-void launch_rebuild(const Buffers& b, int p, int q, const KernelShape& k, double half_skin2,
-                    int half_list, const int32_t* gate, hipStream_t s);
+void launch_rebuild(const Buffers& b, int p, int q, const KernelShape& k, double half_skin2, const int32_t* gate,
+                    hipStream_t s);
 // rdl2 = (r_d + skin)^2 bounds the inner entries (rlist2: every entry).
 // copy_back: the list is built from the sorted state in (p, q) and each own
 // atom's state is copied into (p ^ 1, q ^ 1) (automatic rebuilds, which keep

@@ -726,7 +726,7 @@ void rebuild(md_ctx* c, hipStream_t s, bool check_skin)
     const double guard = c->pr ? 0.4 * c->skin : 0.5 * c->skin;
     const double half_skin2 = (c->have_list && check_skin) ? guard * guard : -1.0;
     Timed tm(c, MD_KT_BUILD, s);
-    launch_rebuild(c->buf, c->p, c->q, k, half_skin2, c->nbr_mode == MD_NBR_HALF_ATOMIC, nullptr, s);
+    launch_rebuild(c->buf, c->p, c->q, k, half_skin2, nullptr, s);
     c->p ^= 1;
     c->q ^= 1;
     if (k.brick)
@@ -766,7 +766,7 @@ void auto_check(md_ctx* c, hipStream_t s)
     const double rdl = std::min(c->rd + c->skin, c->rlist);
     Timed tm(c, MD_KT_BUILD, s);
     launch_skin_check(c->buf, c->p, k, guard * guard, gate, gate_set(c, c->gate_sel ^ 1), s);
-    launch_rebuild(c->buf, c->p, c->q, k, -1.0, half, gate, s);
+    launch_rebuild(c->buf, c->p, c->q, k, -1.0, gate, s);
     launch_build_list(c->buf, c->p ^ 1, c->q ^ 1, k, c->rlist * c->rlist, rdl * rdl, half, gate, 1, s);
     c->gate_sel ^= 1;
 }
