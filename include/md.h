@@ -259,7 +259,9 @@ int md_step(md_ctx *ctx, int32_t nsteps, void *stream);
 int md_state_changed(md_ctx *ctx);
 
 /* Synchronises the stream, checks the device error flags and copies the
- * per-replica energies of the last evaluated state to out[0..R). */
+ * per-replica energies of the last evaluated state to out[0..R).  The copy goes
+ * through the null stream, so it also follows the work on that one and on every
+ * blocking stream. */
 int md_energy(md_ctx *ctx, md_energies *out, void *stream);
 
 /* Per-step energies (paper, "Thermodynamic Quantities": the quantities are
